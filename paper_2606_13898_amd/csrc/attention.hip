@@ -636,51 +636,141 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   attn_store_out<HD, QW, NW>(a, u, wid, lane, o, l);
 }
 
-// fp32 path: one thread per query row, keys/values staged through LDS 32 rows at a time.
-template <int HD>
-__global__ __launch_bounds__(64) void k_attn_f32(const float *__restrict__ qkv,
-                                                 const int *__restrict__ cu, float *__restrict__ out,
-                                                 int heads, int qtiles, float scale_log2) {
-  constexpr int BKV = 32;
-  __shared__ float sK[BKV][HD];
-  __shared__ float sV[BKV][HD];
-  const int qt = blockIdx.x % qtiles;
-  const int sh = blockIdx.x / qtiles;
-  const int h = sh % heads, s = sh / heads;
-  const int lo = cu[s], n = cu[s + 1] - lo;
-  const int q0 = qt * 64;
-  if (q0 >= n) return;
-  const int D = heads * HD;
-  const size_t ld = size_t(3) * D;
-  const int q = min(q0 + int(threadIdx.x), n - 1);
-  float qv[HD], o[HD];
-  for (int d = 0; d < HD; ++d) { qv[d] = qkv[size_t(lo + q) * ld + h * HD + d]; o[d] = 0.f; }
-  float m = -INFINITY, l = 0.f;
-  for (int kv0 = 0; kv0 < n; kv0 += BKV) {
-    __syncthreads();
-    for (int e = threadIdx.x; e < BKV * HD; e += 64) {
-      const int r = e / HD, d = e % HD;
-      const int row = min(kv0 + r, n - 1);
-      sK[r][d] = qkv[size_t(lo + row) * ld + D + h * HD + d];
-      sV[r][d] = qkv[size_t(lo + row) * ld + 2 * D + h * HD + d];
+// fp32 path (v_mfma_f32_16x16x4_f32): a workgroup takes 16 query rows of one (sample, head) and its NW
+// waves every NW-th tile of 16 keys, each with its own running (m, l, O); they merge through LDS at
+// the end.  Fragments come straight from global memory in 16-byte pieces, one tile ahead: S^T = K Q^T
+// leaves query l % 16 and keys 4 (l / 16) + r in a lane, so P is already the second operand of
+// O^T = V^T P^T once MFMA j takes key 4 g + j from lane group g, and output row i of MFMA t holds dim
+// (HD / 16) i + t, which makes a lane's share of a V row contiguous.  Float32 workloads are small, so
+// what bounds the pass is the serial chain over the keys; splitting it over the waves, not LDS
+// staging, is what shortens it.  551 tokens, 4 heads x 64: 650 us with one thread per query row and
+// scalar FMAs, 11 us so.
+template <int HD, int NW>
+__global__ __launch_bounds__(NW * 64) void k_attn_f32(const float *__restrict__ qkv,
+                                                      const int *__restrict__ cu, float *__restrict__ out,
+                                                      int B, int heads, float scale_log2) {
+  constexpr int KF = HD / 16;      // 16-byte pieces of a query or key row per lane
+  constexpr int VF = HD / 64;      // 16-byte pieces of a lane's share of a value row
+  constexpr int LDO = HD + 4;      // LDS row stride (floats): spreads the rows over the banks
+  __shared__ __attribute__((aligned(16))) float sO[NW][16][LDO];
+  __shared__ float sM[NW][16], sL[NW][16];
+  // units (sample, head, query tile) of the lengths that are there, so that the XCDs share them
+  // evenly; the grid is sized for the longest sequences
+  int units = 0;
+  for (int s = 0; s < B; ++s) units += heads * ((cu_at(cu, s + 1) - cu_at(cu, s) + 15) / 16);
+  for (int b = blockIdx.x; b < units; b += gridDim.x) {
+    int unit = xcd_remap(b, units), s = 0, lo = cu_at(cu, 0), n = cu_at(cu, 1) - lo;
+    for (int k; unit >= (k = heads * ((n + 15) / 16)); n = cu_at(cu, s + 1) - lo) {
+      unit -= k;
+      lo = cu_at(cu, ++s);
+    }
+    const int qt = unit % ((n + 15) / 16), h = unit / ((n + 15) / 16);
+    const int q0 = qt * 16;
+    const int D = heads * HD;
+    const size_t ld = size_t(3) * D;
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lr = lane & 15, lg = lane >> 4;
+    const float *base = qkv + size_t(lo) * ld + h * HD;
+
+    f32x4 qf[KF];
+  #pragma unroll
+    for (int c = 0; c < KF; ++c)
+      qf[c] = *reinterpret_cast<const f32x4 *>(base + size_t(min(q0 + lr, n - 1)) * ld + 16 * c + 4 * lg);
+
+    const int ntiles = (n + 15) / 16;
+    auto load = [&](int t, f32x4 (&kf)[KF], f32x4 (&vf)[4][VF]) __attribute__((always_inline)) {
+      const float *kr = base + D + size_t(min(16 * t + lr, n - 1)) * ld + 4 * lg;
+  #pragma unroll
+      for (int c = 0; c < KF; ++c) kf[c] = *reinterpret_cast<const f32x4 *>(kr + 16 * c);
+  #pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float *vr = base + 2 * D + size_t(min(16 * t + 4 * lg + j, n - 1)) * ld + KF * lr;
+  #pragma unroll
+        for (int c = 0; c < VF; ++c) vf[j][c] = *reinterpret_cast<const f32x4 *>(vr + 4 * c);
+      }
+    };
+
+    f32x4 o[KF];
+  #pragma unroll
+    for (int t = 0; t < KF; ++t) o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;  // l: this lane's own keys only, summed over the lane groups at the end
+    auto tile = [&](int t, const f32x4 (&kf)[KF], const f32x4 (&vf)[4][VF]) __attribute__((always_inline)) {
+      f32x4 sa[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};  // two independent chains
+  #pragma unroll
+      for (int c = 0; c < KF; ++c)
+  #pragma unroll
+        for (int j = 0; j < 4; ++j)
+          sa[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][j], qf[c][j], sa[j & 1], 0, 0, 0);
+      f32x4 sc = (sa[0] + sa[1]) * scale_log2;
+      if (16 * t + 16 > n) {
+  #pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (16 * t + 4 * lg + r >= n) sc[r] = -INFINITY;
+      }
+      const float mt = xmax16_32(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])));
+      if (__any(mt > m)) {
+        const float mnew = fmaxf(m, mt);
+        const float alpha = __builtin_amdgcn_exp2f(m - mnew);
+        l *= alpha;
+  #pragma unroll
+        for (int d = 0; d < KF; ++d) o[d] *= alpha;
+        m = mnew;
+      }
+      f32x4 p;
+  #pragma unroll
+      for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(sc[r] - m);
+      l += (p[0] + p[1]) + (p[2] + p[3]);
+  #pragma unroll
+      for (int j = 0; j < 4; ++j)
+  #pragma unroll
+        for (int d = 0; d < KF; ++d)
+          o[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[j][d >> 2][d & 3], p[j], o[d], 0, 0, 0);
+    };
+    // two tiles per turn, so that the fragments alternate between two register sets; a load past the
+    // wave's last tile re-reads the last one
+    f32x4 ka[KF], va[4][VF], kb[KF], vb[4][VF];
+    if (wid < ntiles) {
+      load(wid, ka, va);
+  #pragma unroll 1
+      for (int t = wid; t < ntiles; t += 2 * NW) {
+        load(min(t + NW, ntiles - 1), kb, vb);
+        tile(t, ka, va);
+        if (t + NW >= ntiles) break;
+        load(min(t + 2 * NW, ntiles - 1), ka, va);
+        tile(t + NW, kb, vb);
+      }
+    }
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+  #pragma unroll
+    for (int r = 0; r < 4; ++r)
+  #pragma unroll
+      for (int c = 0; c < VF; ++c)
+        *reinterpret_cast<f32x4 *>(&sO[wid][lr][KF * (4 * lg + r) + 4 * c]) =
+            f32x4{o[4 * c][r], o[4 * c + 1][r], o[4 * c + 2][r], o[4 * c + 3][r]};
+    if (lg == 0) {
+      sM[wid][lr] = m;
+      sL[wid][lr] = l;
     }
     __syncthreads();
-    const int nk = min(BKV, n - kv0);
-    for (int r = 0; r < nk; ++r) {
-      float sdot = 0.f;
-      for (int d = 0; d < HD; ++d) sdot += qv[d] * sK[r][d];
-      const float x = sdot * scale_log2;
-      const float mnew = fmaxf(m, x);
-      const float alpha = exp2f(m - mnew);
-      const float p = exp2f(x - mnew);
-      l = l * alpha + p;
-      for (int d = 0; d < HD; ++d) o[d] = o[d] * alpha + p * sV[r][d];
-      m = mnew;
+    // merge: a thread takes 4 dims of one query row (a wave without a tile has m = -inf, weight 0)
+    for (int e = threadIdx.x; e < 16 * HD / 4; e += NW * 64) {
+      const int q = e / (HD / 4), d = e % (HD / 4) * 4;
+      if (q0 + q >= n) break;
+      float M = sM[0][q];
+  #pragma unroll
+      for (int w = 1; w < NW; ++w) M = fmaxf(M, sM[w][q]);
+      f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+      float L = 0.f;
+  #pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const float c = __builtin_amdgcn_exp2f(sM[w][q] - M);
+        acc += *reinterpret_cast<const f32x4 *>(&sO[w][q][d]) * c;
+        L += sL[w][q] * c;
+      }
+      *reinterpret_cast<f32x4 *>(out + size_t(lo + q0 + q) * D + h * HD + d) = acc * (1.0f / L);
     }
-  }
-  if (q0 + int(threadIdx.x) < n) {
-    const float inv = 1.0f / l;
-    for (int d = 0; d < HD; ++d) out[size_t(lo + q) * D + h * HD + d] = o[d] * inv;
+    __syncthreads();  // the next unit's waves write the same LDS
   }
 }
 
@@ -721,13 +811,14 @@ static hipError_t run_attn_bf16(const void *qkv, const int *cu, void *out, float
 template <int HD>
 static hipError_t run_attn_f32(const void *qkv, const int *cu, void *out, int B, int heads,
                                int max_seq, hipStream_t st) {
-  const int qtiles = (max_seq + 63) / 64;
+  const int qtiles = (max_seq + 15) / 16;
   const long long nblk = (long long)B * heads * qtiles;
   if (nblk <= 0) return hipSuccess;
   const float sl2 = kLog2e / sqrtf(float(HD));
-  hipLaunchKernelGGL((k_attn_f32<HD>), dim3(unsigned(nblk)), dim3(64), 0, st,
+  // the grid is bounded (its threads must stay below 2^32); larger problems loop
+  hipLaunchKernelGGL((k_attn_f32<HD, 8>), dim3(unsigned(nblk < (1 << 20) ? nblk : (1 << 20))), dim3(512), 0, st,
                      reinterpret_cast<const float *>(qkv), cu, reinterpret_cast<float *>(out),
-                     heads, qtiles, sl2);
+                     B, heads, sl2);
   return hipGetLastError();
 }
 

@@ -12,7 +12,7 @@
 // global->LDS loads (192 x 192 tiles: 128-byte K-step windows, both stages of a row's K step
 // together, through a 3-slot ring).  Whole data-parallel waves of tiles run first, then a stream-K remainder;
 // cut tiles leave fp32 partials that k_gemm_fix adds in a fixed order before the epilogue.
-// float32 path: a plain LDS-tiled FMA kernel for the small float32 workloads.
+// float32 path: v_mfma_f32_16x16x4_f32 straight from global memory, K split over a workgroup's waves.
 #include <type_traits>
 
 #include "common.h"
@@ -30,29 +30,10 @@ HILO_DEV float gelu_tanh(float u) {
   return u * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
 }
 
-// Row range of row-tile t: tiles of sample s are [image tiles][text tiles].
+// Row range of a row tile; tiles of a sample are [image tiles][text tiles].
 struct TileRows {
   int s, sigma, row0, nrows;
 };
-
-HILO_DEV TileRows tile_rows(const int *cu, int L, int imgTiles, int txtTiles, int BM, int t) {
-  TileRows tr;
-  const int per = imgTiles + txtTiles;
-  tr.s = t / per;
-  const int lt = t % per;
-  const int lo = cu[tr.s], hi = cu[tr.s + 1];
-  const int tstart = hi - L;
-  if (lt < imgTiles) {
-    tr.sigma = 0;
-    tr.row0 = lo + lt * BM;
-    tr.nrows = min(BM, tstart - tr.row0);
-  } else {
-    tr.sigma = 1;
-    tr.row0 = tstart + (lt - imgTiles) * BM;
-    tr.nrows = min(BM, hi - tr.row0);
-  }
-  return tr;
-}
 
 template <int EPI, bool BF16OUT>
 HILO_DEV void epilogue4(const GemmProblem &p, const TileRows &tr, int m, int n, const float *acc) {
@@ -1126,50 +1107,84 @@ __global__ __launch_bounds__(kFixThreads) void k_gemm_fix(GemmProblem p, int P) 
 
 // ------------------------------------------------------------------------------- fp32 path
 
-// Plain LDS-tiled fp32 FMA kernel for the float32 problem sizes: 64 x 64 tile, 256 threads, 4 x 4
-// outputs per thread.
+// v_mfma_f32_16x16x4_f32 on fragments read straight from global memory: lane (r, g) = (l % 16, l / 16)
+// takes 16 bytes of row r at K offset 4 g of every 16, and MFMA j of the four multiplies element j of
+// both operands (any order of K will do as long as both agree), so no LDS staging and no barrier
+// stands between the loads and the matrix core.  A workgroup's tile is 32 x 32 and its 4 waves take a
+// quarter of K each (their sums meet in LDS): the float32 problems are small, and what bounds them is
+// the serial chain of one wave -- K / 16 steps of 16 MFMAs -- and too few waves, not bandwidth.
+// 551 rows (32 x 32 grid, D 256, MLP 1024), against the LDS-tiled scalar FMA kernel on 64 x 64 tiles
+// before: QKV 29.7 -> 8.5 us, output 30 -> 6, MLP up 33 -> 11, MLP down 110 -> 12.5.
 template <int EPI>
-__global__ __launch_bounds__(256) void k_gemm_f32(GemmProblem p, int imgTiles, int txtTiles,
-                                                  int tilesN) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float sA[BK][BM + 4];
-  __shared__ float sB[BK][BN + 4];
-  const int bid = blockIdx.x;
-  const int tn = bid % tilesN;
-  const TileRows tr = tile_rows(p.cu, p.L, imgTiles, txtTiles, BM, bid / tilesN);
-  if (tr.nrows <= 0) return;
-  const int n0 = tn * BN;
-  const float *A = reinterpret_cast<const float *>(p.A);
-  const float *Wt = reinterpret_cast<const float *>(p.W[tr.sigma]);
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < p.K; k0 += BK) {
-    for (int e = tid; e < BM * BK; e += 256) {
-      const int r = e / BK, k = e % BK;
-      sA[k][r] = A[size_t(tr.row0 + min(r, tr.nrows - 1)) * p.lda + k0 + k];
-      sB[k][r] = Wt[size_t(min(n0 + r, p.N - 1)) * p.K + k0 + k];
+__global__ __launch_bounds__(256) void k_gemm_f32(GemmProblem p) {
+  constexpr int BM = 32, BN = 32, CH = 4;  // CH: 16-deep K steps loaded ahead
+  __shared__ f32x4 part[4][4][64];
+  // tiles of the rows that are there, so that the XCDs share them evenly; the grid is sized for the
+  // longest sequences
+  const int tilesN = p.N / BN, tiles = row_tiles_total(p, BM) * tilesN;
+  for (int b = blockIdx.x; b < tiles; b += gridDim.x) {
+    const int tile = xcd_remap(b, tiles), tn = tile % tilesN;
+    const TileRows tr = decode_row_tile(p, BM, tile / tilesN);
+    const int n0 = tn * BN;  // N % 64 == 0: the tile's columns all exist
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lr = lane & 15, lg = lane >> 4;
+    const float *A[2], *W[2];
+  #pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      A[i] = reinterpret_cast<const float *>(p.A) + size_t(tr.row0 + min(16 * i + lr, tr.nrows - 1)) * p.lda + 4 * lg;
+      W[i] = reinterpret_cast<const float *>(tr.sigma ? p.W[1] : p.W[0]) + size_t(n0 + 16 * i + lr) * p.K + 4 * lg;
     }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < BK; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) { a[u] = sA[k][ty * 4 + u]; b[u] = sB[k][tx * 4 + u]; }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] += a[u] * b[v];
+    const int steps = p.K / 16, s0 = steps * wid / 4, s1 = steps * (wid + 1) / 4;  // K % 64 == 0: never empty
+    f32x4 acc[2][2];
+  #pragma unroll
+    for (int i = 0; i < 2; ++i)
+  #pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto load = [&](int s, f32x4 (&a)[CH][2], f32x4 (&w)[CH][2]) __attribute__((always_inline)) {
+  #pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        const int k = 16 * min(s + c, s1 - 1);  // past the wave's range: re-read its last step
+  #pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          a[c][i] = *reinterpret_cast<const f32x4 *>(A[i] + k);
+          w[c][i] = *reinterpret_cast<const f32x4 *>(W[i] + k);
+        }
+      }
+    };
+    auto mul = [&](int s, const f32x4 (&a)[CH][2], const f32x4 (&w)[CH][2]) __attribute__((always_inline)) {
+  #pragma unroll
+      for (int c = 0; c < CH; ++c)
+        if (s + c < s1) {
+  #pragma unroll
+          for (int e = 0; e < 4; ++e)
+  #pragma unroll
+            for (int i = 0; i < 2; ++i)
+  #pragma unroll
+              for (int j = 0; j < 2; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[c][j][e], a[c][i][e], acc[i][j], 0, 0, 0);
+        }
+    };
+    f32x4 xa[CH][2], xw[CH][2], ya[CH][2], yw[CH][2];
+    load(s0, xa, xw);
+  #pragma unroll 1
+    for (int s = s0; s < s1; s += 2 * CH) {
+      if (s + CH < s1) load(s + CH, ya, yw);
+      mul(s, xa, xw);
+      if (s + CH >= s1) break;
+      if (s + 2 * CH < s1) load(s + 2 * CH, xa, xw);
+      mul(s + CH, ya, yw);
     }
+  #pragma unroll
+    for (int i = 0; i < 2; ++i)
+  #pragma unroll
+      for (int j = 0; j < 2; ++j) part[wid][2 * i + j][lane] = acc[i][j];
     __syncthreads();
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int rl = ty * 4 + u;
-    if (rl >= tr.nrows) continue;
-    const int n = n0 + tx * 4;
-    if (n >= p.N) continue;
-    epilogue4<EPI, false>(p, tr, tr.row0 + rl, n, acc[u]);
+    // wave w finishes subtile w: rows 16 (w / 2) + lr, columns 16 (w % 2) + 4 lg .. + 3
+    const f32x4 v = (part[0][wid][lane] + part[1][wid][lane]) + (part[2][wid][lane] + part[3][wid][lane]);
+    const int rl = 16 * (wid >> 1) + lr;
+    const float out[4] = {v[0], v[1], v[2], v[3]};
+    if (rl < tr.nrows) epilogue4<EPI, false>(p, tr, tr.row0 + rl, n0 + 16 * (wid & 1) + 4 * lg, out);
+    __syncthreads();  // the next tile's waves write the same LDS
   }
 }
 
@@ -1209,13 +1224,10 @@ static hipError_t run_big(const GemmProblem &p, hipStream_t st) {
 
 template <int EPI>
 static hipError_t run_f32(const GemmProblem &p, hipStream_t st) {
-  const int imgTiles = (p.max_img_rows + 63) / 64;
-  const int txtTiles = (p.L + 63) / 64;
-  const int tilesN = (p.N + 63) / 64;
-  const long long nblk = (long long)p.B * (imgTiles + txtTiles) * tilesN;
+  const long long nblk = (long long)p.B * ((p.max_img_rows + 31) / 32 + (p.L + 31) / 32) * (p.N / 32);
   if (nblk <= 0) return hipSuccess;
-  hipLaunchKernelGGL((k_gemm_f32<EPI>), dim3(unsigned(nblk)), dim3(256), 0, st, p, imgTiles,
-                     txtTiles, tilesN);
+  // the grid is bounded (its threads must stay below 2^32); larger problems loop
+  hipLaunchKernelGGL((k_gemm_f32<EPI>), dim3(unsigned(nblk < (1 << 20) ? nblk : (1 << 20))), dim3(256), 0, st, p);
   return hipGetLastError();
 }
 

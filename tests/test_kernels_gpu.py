@@ -1,0 +1,58 @@
+"""Single kernels at the sizes where their tiling can go wrong, against the float64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import hilo_oracle as O
+from paper_2606_13898_amd import hilo, inputs
+from parity_util import assert_close, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def _cu(lens):
+    return np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+
+
+# 16 queries per workgroup, 16-key tiles dealt to 8 waves: waves without a tile, a lone last key,
+# whole rounds of tiles, and more units than an XCD's share
+@pytest.mark.parametrize("hd,lens,heads", [(64, [1, 15, 16, 17, 0, 33], 2), (128, [2, 127, 128, 129], 2),
+                                           (64, [257, 600], 4), (128, [511], 1)])
+def test_attention_core_f32(hd, lens, heads):
+    print(f"[kernel] float32 attention core hd={hd} heads={heads} lens={lens}", flush=True)
+    cu, D = _cu(lens), heads * hd
+    qkv = np.random.default_rng(hd + len(lens)).standard_normal((int(cu[-1]), 3 * D)).astype(np.float32)
+    shp = hilo.hilo_shape(len(lens), 1, 2, 2 * ((max(lens) + 3) // 4), 0, D, heads, hd, 4 * D, hilo.F32)
+    out = torch.full((int(cu[-1]), D), float("nan"), device="cuda")
+    hilo.hilo_attention_core(shp, torch.from_numpy(qkv).cuda(), torch.from_numpy(cu).cuda(), out)
+    torch.cuda.synchronize()
+    assert_close(to_np(out), O.attention_core(qkv, cu, heads), "f32", "float32 attention core")
+
+
+def run_mlp(shape, lens, seed):
+    """hilo_mlp on packed rows of the given sample lengths -> (z after, oracle's z)."""
+    rng = np.random.default_rng(seed)
+    cu, D = _cu(lens), shape.dim
+    z = rng.standard_normal((int(cu[-1]), D)).astype(np.float32)
+    w = inputs.block_weights(rng, D, shape.mlp_dim, shape.dtype)
+    mod = inputs.modulation(rng, shape.batch, D)
+    dt = torch.float32 if shape.dtype == "f32" else torch.bfloat16
+    dev = [{k: torch.from_numpy(v).to(dt).cuda() for k, v in s.items()} for s in w]
+    sh = hilo.make_shape(shape)
+    zd = torch.from_numpy(z).cuda()
+    ws = torch.empty(hilo.hilo_workspace_bytes(sh), dtype=torch.uint8, device="cuda")
+    hilo.hilo_mlp(sh, zd, torch.from_numpy(cu).cuda(), hilo.mlp_weights(dev), torch.from_numpy(mod).cuda(), ws)
+    torch.cuda.synchronize()
+    want = O.mlp(z.astype(np.float64), np.arange(int(cu[-1])), cu, shape.text_len, w, mod)
+    return to_np(zd), want
+
+
+# 32 x 32 tiles, K split over 4 waves in steps of 16 (D 64: one step per wave; 192: three, less than
+# a load chunk), row tails on either side of a tile's edge, with and without text rows
+@pytest.mark.parametrize("dim,mlp,lens,text", [(64, 64, [1, 32, 33], 0), (192, 320, [40, 103, 64], 31),
+                                               (256, 1024, [97, 66], 33)])
+def test_mlp_f32(dim, mlp, lens, text):
+    print(f"[kernel] float32 MLP dim={dim} mlp={mlp} lens={lens} text={text}", flush=True)
+    shape = inputs.BlockShape(len(lens), 1, 2, 2 * ((max(lens) + 3) // 4), text, dim, dim // 64, 64, mlp, "f32")
+    got, want = run_mlp(shape, lens, 3)
+    assert_close(got, want, "f32", "float32 MLP")
