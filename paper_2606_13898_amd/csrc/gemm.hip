@@ -4,14 +4,14 @@
 // gated residual update of the float32 stream z; for the FP8 block's QKV projection, the q and k
 // columns leave as E4M3 codes with a power-of-two scale per (row, head).
 //
-// bf16 and FP8 paths: one MFMA kernel (k_gemm_big), one persistent workgroup per CU with 4 waves,
-// 192 x 192 tiles (every projection but the FP8 QKV) or 256 x 256 (the FP8 QKV, which writes FP8
-// q / k with one scale per row and head: a wave's 128 columns hold whole heads) as
-// 32 x 32 MFMA blocks (v_mfma_f32_32x32x16_bf16, or v_mfma_f32_32x32x64_f8f6f4 on E4M3 codes),
-// fp32 accumulators in AGPRs, K in 64-byte stages through a 4-slot LDS ring filled by direct
-// global->LDS loads (192 x 192 tiles: 128-byte K-step windows, both stages of a row's K step
-// together, through a 3-slot ring).  Whole data-parallel waves of tiles run first, then a stream-K remainder;
-// cut tiles leave fp32 partials that k_gemm_fix adds in a fixed order before the epilogue.
+// bf16 path (k_gemm8): one persistent workgroup of 8 waves per CU, 256 x 256 or 192 x 192 tiles (chosen
+// on the device from the row counts), K through LDS in 128-byte windows filled by direct global->LDS
+// loads, fragments read half a window ahead of their MFMAs.
+// FP8 path (k_gemm_big): one persistent workgroup of 4 waves per CU, 192 x 192 tiles, or 256 x 256 for
+// the QKV projection (which writes FP8 q / k with one scale per row and head: a wave's 128 columns hold
+// whole heads), v_mfma_f32_32x32x64_f8f6f4 on E4M3 codes, fp32 accumulators in AGPRs.
+// Both: whole data-parallel waves of tiles run first, then a stream-K remainder; cut tiles leave fp32
+// partials that a fixup kernel adds in a fixed order before the epilogue.
 // float32 path: v_mfma_f32_16x16x4_f32 straight from global memory, K split over a workgroup's waves.
 #include <type_traits>
 
@@ -117,7 +117,8 @@ HILO_DEV TileRows decode_row_tile(const GemmProblem &p, int BM, int r) {
   return tr;
 }
 
-// Schedule of the bf16 projections over P persistent workgroups (one per CU).  A unit is one
+// Schedule of the projections over P = kGemmWorkgroups persistent workgroups (one per CU; a constant, so
+// that the divisions by it are shifts and the prologue of every launch stays short).  A unit is one
 // K piece of one output tile: tiles are cut into s pieces when there are fewer tiles than
 // workgroups (s = ceil(P / tiles), at most one K step per piece), else s = 1.  Units are ordered
 // piece-major, row tile fastest within a piece.  The first floor(U / P) * P units run
@@ -145,7 +146,8 @@ constexpr int kNoSplitSteps = 64;
 // at 256 x 256) that the fixup reads back, so a short tail goes to fewer workgroups.
 constexpr int kSkMinSteps = 12;
 
-HILO_DEV SkPlan sk_plan(const GemmProblem &p, int BM, int BN, int P, int kstep = 64) {
+HILO_DEV SkPlan sk_plan(const GemmProblem &p, int BM, int BN, int kstep = 64) {
+  constexpr int P = kGemmWorkgroups;
   SkPlan q;
   q.R = row_tiles_total(p, BM);
   q.TN = (p.N + BN - 1) / BN;
@@ -183,13 +185,10 @@ struct SkRange {
   long long beg, end;
 };
 
-HILO_DEV SkRange sk_range(long long I, int P, int w) {
-  return SkRange{I * w / P, I * (w + 1) / P};
-}
-
 // Workgroup w's stream-K range under plan q (empty past the plan's Pk workgroups).
 HILO_DEV SkRange sk_range(const SkPlan &q, int w) {
-  return w < q.Pk ? sk_range(q.I, q.Pk, w) : SkRange{q.I, q.I};
+  if (w >= q.Pk || q.I == 0) return SkRange{q.I, q.I};
+  return SkRange{q.I * w / q.Pk, q.I * (w + 1) / q.Pk};
 }
 
 // The workgroup whose stream-K range holds iteration a.
@@ -224,14 +223,15 @@ struct SkCursor {
   long long it;   // next stream-K iteration
 };
 
-HILO_DEV SkItem sk_next_item(SkCursor &c, const SkPlan &q, const SkRange &rg, int P, int pid, float *part,
+HILO_DEV SkItem sk_next_item(SkCursor &c, const SkPlan &q, const SkRange &rg, int pid, float *part,
                              size_t part_floats) {
+  constexpr int P = kGemmWorkgroups;
   SkItem x{0, 0, 0, nullptr, false};
   if (c.u < q.dp) {
-    const int pc = c.u / q.T;
+    const int pc = q.s == 1 ? 0 : c.u / q.T;
     x.t = c.u - pc * q.T;
-    x.kb = piece_k0(q, pc);
-    x.ke = piece_k0(q, pc + 1);
+    x.kb = q.s == 1 ? 0 : piece_k0(q, pc);
+    x.ke = q.s == 1 ? q.nk : piece_k0(q, pc + 1);
     x.slot = q.s == 1 ? nullptr : part + size_t(c.u) * part_floats;
     x.valid = true;
     c.u += P;
@@ -254,11 +254,15 @@ HILO_DEV SkItem sk_next_item(SkCursor &c, const SkPlan &q, const SkRange &rg, in
 
 // Partial tiles of a BM x BN tile on WM x WN waves, in the 16 x 16 fragment order the fixup
 // reads, and the fixup's epilogue of one fragment row.
-template <int BM, int BN, int WM, int WN>
+// CONTIG: a lane's columns of all fragment columns are consecutive (the 8-wave kernel), instead of 4 of
+// every 16.
+template <int BM, int BN, int WM, int WN, bool CONTIG = false>
 struct SkTile {
   static constexpr int NW = WM * WN;
   static constexpr int TM = BM / WM / 16;
   static constexpr int TN = BN / WN / 16;
+  static constexpr int CS = CONTIG ? 4 : 16;       // columns between fragment columns
+  static constexpr int CL = CONTIG ? 4 * TN : 4;   // columns between the lane groups
   static constexpr size_t kPartFloats = size_t(BM) * BN;
 
   // partial-sum slot layout: register order, one float4 per lane per (wave, i, j)
@@ -323,14 +327,14 @@ struct SkTile {
   HILO_DEV static void epilogue_rows(const GemmProblem &p, const TileRows &tr, int n0, int wid, int i0,
                                      int lane, const f32x4 (&acc)[ROWS][TN]) {
     const int rbase = (wid / WN) * (BM / WM) + i0 * 16 + (lane & 15);
-    const int cbase = n0 + (wid % WN) * (BN / WN) + 4 * (lane >> 4);
+    const int cbase = n0 + (wid % WN) * (BN / WN) + CL * (lane >> 4);
     const uint16_t *bias = reinterpret_cast<const uint16_t *>(p.bias[tr.sigma]);
     float bv[TN][4];
     float4 gt[TN];
     float4 zv[ROWS][TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const int nc = min(cbase + j * 16, p.N - 4);
+      const int nc = min(cbase + j * CS, p.N - 4);
       const uint2 bu = *reinterpret_cast<const uint2 *>(bias + nc);
       bv[j][0] = __uint_as_float(bu.x << 16); bv[j][1] = __uint_as_float(bu.x & 0xffff0000u);
       bv[j][2] = __uint_as_float(bu.y << 16); bv[j][3] = __uint_as_float(bu.y & 0xffff0000u);
@@ -342,7 +346,7 @@ struct SkTile {
     if constexpr (F8) {
       const float *ws = tr.sigma ? p.w_scale[1] : p.w_scale[0];
 #pragma unroll
-      for (int j = 0; j < TN; ++j) wsc[j] = *reinterpret_cast<const float4 *>(ws + min(cbase + j * 16, p.N - 4));
+      for (int j = 0; j < TN; ++j) wsc[j] = *reinterpret_cast<const float4 *>(ws + min(cbase + j * CS, p.N - 4));
 #pragma unroll
       for (int i = 0; i < ROWS; ++i) asc[i] = p.a_scale[tr.row0 + min(rbase + i * 16, tr.nrows - 1)];
     }
@@ -352,7 +356,7 @@ struct SkTile {
         const size_t m = size_t(tr.row0 + min(rbase + i * 16, tr.nrows - 1));
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-          zv[i][j] = *reinterpret_cast<const float4 *>(p.z + m * p.ldz + min(cbase + j * 16, p.N - 4));
+          zv[i][j] = *reinterpret_cast<const float4 *>(p.z + m * p.ldz + min(cbase + j * CS, p.N - 4));
       }
     }
 #pragma unroll
@@ -362,7 +366,7 @@ struct SkTile {
       const size_t m = size_t(tr.row0 + rl);
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
-        const int n = cbase + j * 16;
+        const int n = cbase + j * CS;
         if (n >= p.N) continue;
         float v[4];
         if constexpr (F8) {
@@ -711,9 +715,8 @@ __global__ __launch_bounds__(256) void k_gemm_big(GemmProblem p) {
   constexpr int ESZ = F8 ? 1 : 2;       // operand bytes per element
   __shared__ __attribute__((aligned(1024))) uint8_t lds[G::LDS];
 
-  const int P = gridDim.x;
-  const int pid = xcd_remap(blockIdx.x, P);
-  const SkPlan q = sk_plan(p, BM, BN, P, F8 ? 128 : 64);
+  const int pid = xcd_remap(blockIdx.x, kGemmWorkgroups);
+  const SkPlan q = sk_plan(p, BM, BN, F8 ? 128 : 64);
   const SkRange rg = sk_range(q, pid);
 
   const int lane = threadIdx.x & 63;
@@ -758,7 +761,7 @@ __global__ __launch_bounds__(256) void k_gemm_big(GemmProblem p) {
     }
   };
   auto ld_advance = [&]() __attribute__((always_inline)) {
-    const SkItem x = uni(sk_next_item(lc, q, rg, P, pid, p.part, T::kPartFloats));
+    const SkItem x = uni(sk_next_item(lc, q, rg, pid, p.part, T::kPartFloats));
     if (x.valid) {
       ld_src(x.t);
       lk = WIN ? x.kb : 2 * x.kb;
@@ -915,7 +918,7 @@ __global__ __launch_bounds__(256) void k_gemm_big(GemmProblem p) {
   };
 
   SkCursor cc{pid, rg.beg};
-  SkItem cur = uni(sk_next_item(cc, q, rg, P, pid, p.part, T::kPartFloats));
+  SkItem cur = uni(sk_next_item(cc, q, rg, pid, p.part, T::kPartFloats));
   if (!cur.valid) return;
   ld_advance();  // the same first item
   if constexpr (WIN) {
@@ -1007,10 +1010,337 @@ __global__ __launch_bounds__(256) void k_gemm_big(GemmProblem p) {
           asm volatile("" ::: "memory");
         }
     }
-    cur = uni(sk_next_item(cc, q, rg, P, pid, p.part, T::kPartFloats));
+    cur = uni(sk_next_item(cc, q, rg, pid, p.part, T::kPartFloats));
     if (!cur.valid) break;
   }
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+}
+
+// ------------------------------------------------------------------ bf16 tiles on eight waves
+//
+// One persistent workgroup of 8 waves per CU (2 x 4: wave tile BM/2 x BN/4 as 16 x 16 MFMA blocks, two
+// waves per SIMD).  A K step is a window of 64 values, 128-byte rows of A and W; LDS holds SLOTS windows
+// filled by direct global->LDS loads of 8 whole lines each (16-byte chunk c of row r at c ^ (r / 2) % 8,
+// so that the 16 rows a fragment read touches fall on 16 bank groups, natural or permuted order alike).
+// A window is two halves of 32 values; while the MFMAs of one half run, the fragments of the next are
+// read into the other register set, a few between the rows of blocks, so the matrix core of a SIMD waits
+// for LDS only where both of its waves do.  One barrier per window, between its halves: by then every
+// wave has read the window (its slot is refilled during the second half) and the next window has landed.
+//
+// What bounds it: the matrix core at the clock the power limit leaves (MFMAs alone 2.05 PFLOP/s on
+// random data), the fragment reads and the L2-to-LDS path in about equal parts -- without the reads or
+// without the loads the 256 x 256 loop runs 12-15% faster, without either 30%.  A CU takes in ~120 GB/s
+// of L2 hits and ~30 GB/s of misses, so the bytes per FLOP of the tile matter: 23040 x 12288 x 3072 runs
+// 1247 us on 256 x 256 tiles (1.40 PFLOP/s), 1391 on 192 x 192; the 4-wave loop before took ~1750 (192 x
+// 192, one wave per SIMD: every memory instruction held its only MFMA stream).  Two 4-wave groups in
+// ping-pong (one in its MFMAs, the other reading) ran 1370 and 1347 us; 32 x 32 MFMAs in this schedule
+// 1367; s_setprio around the MFMAs cost 1%.
+namespace g8 {
+constexpr int kEpi = 512;  // per wave, behind the windows: 64 columns of bias (bf16), then of the gate (float32)
+template <int BM, int BN>
+struct Geo {
+  static constexpr int MB = BM / 32, NB = BN / 64;  // 16 x 16 blocks per wave
+  static constexpr int LA = BM / 64, LB = BN / 64;  // load instructions per wave and window
+  static constexpr int WB = (BM + BN) * 128;        // bytes of a window
+  static constexpr int SLOTS = 3 * WB + 8 * kEpi <= 160 * 1024 ? 3 : 2;
+  static constexpr int LDS = SLOTS * WB + 8 * kEpi;
+};
+HILO_DEV int swz(int r) { return (r >> 1) & 7; }
+template <int V>
+struct Int {
+  static constexpr int value = V;
+};
+template <int N>
+HILO_DEV void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+}  // namespace g8
+
+template <int OFF>
+HILO_DEV void ds_read16(bf16x8 &d, uint32_t addr) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF) : "memory");
+}
+
+// All work items of this workgroup under plan q on BM x BN tiles.
+template <int BM, int BN, int EPI>
+HILO_DEV void gemm8_run(const GemmProblem &p, const SkPlan &q, int pid, uint8_t *lds) {
+  using namespace g8;
+  using G = Geo<BM, BN>;
+  using T = SkTile<BM, BN, 2, 4, true>;
+  constexpr int MB = G::MB, NB = G::NB, LA = G::LA, LB = G::LB, WB = G::WB, S = G::SLOTS;
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lg = lane >> 4, wm = wid >> 2, wn = wid & 3;
+  const SkRange rg = sk_range(q, pid);
+
+  // ---- loader: its own cursor over the items, S windows ahead of the MFMAs; wave wid loads rows
+  // wid BM/8 .. of A and wid BN/8 .. of W, 8 rows per instruction: a uniform base plus a lane offset
+  SkCursor lc{pid, rg.beg};
+  const char *la = nullptr, *lb = nullptr;
+  uint32_t oa[LA], ob[LB];
+  int lk = 0, lke = 0, lslot = 0;
+  auto ld_advance = [&]() __attribute__((always_inline)) {
+    const SkItem x = uni(sk_next_item(lc, q, rg, pid, p.part, T::kPartFloats));
+    if (!x.valid) {  // no further item: repeat the last window (its slots are free, its addresses valid)
+      --lk;
+      la -= 128;
+      lb -= 128;
+      return;
+    }
+    int rt, tn;
+    tile_coords(q, x.t, rt, tn);
+    const TileRows tr = uni(decode_row_tile(p, BM, uni(rt)));
+    const int n0 = uni(tn) * BN;
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+      const int r = wid * (BM / 8) + 8 * i + (lane >> 3);
+      oa[i] = uint32_t(min(r, tr.nrows - 1)) * uint32_t(p.lda) * 2 + uint32_t((lane & 7) ^ swz(r)) * 16;
+    }
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+      const int r = wid * (BN / 8) + 8 * i + (lane >> 3);
+      ob[i] = uint32_t(min(r, p.N - 1 - n0)) * uint32_t(p.K) * 2 + uint32_t((lane & 7) ^ swz(r)) * 16;
+    }
+    la = reinterpret_cast<const char *>(p.A) + (size_t(tr.row0) * p.lda + size_t(x.kb) * 64) * 2;
+    lb = reinterpret_cast<const char *>(tr.sigma ? p.W[1] : p.W[0]) + (size_t(n0) * p.K + size_t(x.kb) * 64) * 2;
+    lk = x.kb;
+    lke = x.ke;
+  };
+  auto ld_a = [&]() __attribute__((always_inline)) {
+    uint8_t *d = lds + lslot * WB + wid * (BM / 8) * 128;
+#pragma unroll
+    for (int i = 0; i < LA; ++i) g2lds16(la + oa[i], d + i * 1024);
+    la += 128;
+  };
+  auto ld_b = [&]() __attribute__((always_inline)) {
+    uint8_t *d = lds + lslot * WB + (BM + wid * (BN / 8)) * 128;
+#pragma unroll
+    for (int i = 0; i < LB; ++i) g2lds16(lb + ob[i], d + i * 1024);
+    lb += 128;
+    ++lk;
+    lslot = lslot == S - 1 ? 0 : lslot + 1;
+  };
+
+  // ---- fragments: lane (lr, lg) holds chunk 4 h + lg of row lr of a 16-row block.  W rows go in the
+  // order that gives the lane's accumulators 4 NB consecutive columns: MFMA output row 4 g + e of block
+  // j is column 4 NB g + 4 j + e of the wave
+  const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+  uint32_t fa[2], fb[NB][2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    fa[h] = lds0 + (wm * (BM / 2) + lr) * 128 + (((4 * h + lg) ^ swz(lr)) * 16);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int r = wn * (BN / 4) + (lr >> 2) * 4 * NB + 4 * j + (lr & 3);
+      fb[j][h] = lds0 + (BM + r) * 128 + (((4 * h + lg) ^ swz(r)) * 16);
+    }
+  }
+  f32x4 acc[MB][NB];
+  bf16x8 a[2][MB], b[2][NB];
+  uint32_t so = 0;  // byte offset of the window being read
+  // read x of the fragments of half h: W first, then A
+  auto rd = [&](auto hh, auto xx) __attribute__((always_inline)) {
+    constexpr int h = decltype(hh)::value, x = decltype(xx)::value;
+    if constexpr (x < NB) ds_read16<0>(b[h][x], fb[x][h] + so);
+    else if constexpr (x < NB + MB) ds_read16<(x - NB) * 2048>(a[h][x - NB], fa[h] + so);
+  };
+  auto rd_wait = [&](auto hh) __attribute__((always_inline)) {
+    constexpr int h = decltype(hh)::value;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < MB; ++i) asm volatile("" : "+v"(a[h][i]));
+#pragma unroll
+    for (int j = 0; j < NB; ++j) asm volatile("" : "+v"(b[h][j]));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // the MFMAs of half h; after each row of blocks a share of the reads of the other half, and (ld) the
+  // loads of a window into the slot just freed
+  auto half = [&](auto hh, bool ld) __attribute__((always_inline)) {
+    constexpr int h = decltype(hh)::value;
+    constexpr int RPB = (MB + NB + MB - 2) / (MB - 1);  // reads per row of blocks, none after the last
+    auto row = [&](auto ii) __attribute__((always_inline)) {
+      constexpr int i = decltype(ii)::value;
+      if constexpr (i < MB) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[h][j], a[h][i], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        rd(Int<1 - h>{}, Int<i * RPB>{});
+        static_assert(RPB == 2, "reads per row of blocks");
+        rd(Int<1 - h>{}, Int<i * RPB + 1>{});
+        if (h == 1 && i == 0) ld_a();
+        if (h == 1 && i == MB / 2) ld_b();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    row(Int<0>{}); row(Int<1>{}); row(Int<2>{}); row(Int<3>{});
+    row(Int<4>{}); row(Int<5>{}); row(Int<6>{}); row(Int<7>{});
+  };
+
+  // ---- epilogue operands of the current item: the wave's columns of bias and gate, by DMA
+  uint8_t *epi = lds + S * WB + wid * kEpi;
+  SkCursor cc{pid, rg.beg};
+  SkItem cur = uni(sk_next_item(cc, q, rg, pid, p.part, T::kPartFloats));
+  if (!cur.valid) return;
+  ld_advance();  // the same first item
+#pragma unroll 1
+  for (int w = 0; w < S; ++w) {
+    if (lk == lke) ld_advance();
+    ld_a();
+    ld_b();
+  }
+  wait_vm<(S - 1) * (LA + LB)>();
+  asm volatile("s_barrier" ::: "memory");
+  TileRows etr{0, 0, 0, 1};
+  int en0 = 0;
+  while (true) {
+    const bool whole = cur.slot == nullptr;
+    if (whole) {
+      int rt, tn;
+      tile_coords(q, cur.t, rt, tn);
+      en0 = uni(tn) * BN + wn * (BN / 4);
+      etr = uni(decode_row_tile(p, BM, uni(rt)));
+      const uint16_t *bias = reinterpret_cast<const uint16_t *>(etr.sigma ? p.bias[1] : p.bias[0]);
+      g2lds4(bias + min(en0 + 2 * (lane & 31), p.N - 2), epi);
+      if constexpr (EPI == EPI_RESID)
+        g2lds4(p.mod + (size_t(etr.s * 2 + etr.sigma) * 6 + p.gate_idx) * p.D + min(en0 + lane, p.N - 1), epi + 256);
+    }
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the first window's first fragments (again, after an epilogue: it needs their registers)
+    auto r0 = [&](auto x) __attribute__((always_inline)) { rd(Int<0>{}, x); };
+    r0(Int<0>{}); r0(Int<1>{}); r0(Int<2>{}); r0(Int<3>{}); r0(Int<4>{}); r0(Int<5>{});
+    r0(Int<6>{}); r0(Int<7>{}); r0(Int<8>{}); r0(Int<9>{}); r0(Int<10>{}); r0(Int<11>{});
+    rd_wait(Int<0>{});
+#pragma unroll 1
+    for (int kt = cur.kb; kt < cur.ke; ++kt) {
+      half(Int<0>{}, false);
+      rd_wait(Int<1>{});
+      // window kt is read by this wave; all but the last window issued have landed (the epilogue's DMA,
+      // issued behind that one, only makes this wait stricter)
+      wait_vm<(S - 2) * (LA + LB)>();
+      asm volatile("s_barrier" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      so = so == (S - 1) * WB ? 0 : so + WB;
+      if (lk == lke) ld_advance();
+      half(Int<1>{}, true);
+      rd_wait(Int<0>{});
+    }
+    if (whole) {
+      // a one-step item's epilogue operands may still be in flight
+      if (cur.ke - cur.kb < 2) wait_vm<0>();
+      uint2 bu[NB];
+      f32x4 gv[NB];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        bu[j] = *reinterpret_cast<const uint2 *>(epi + 2 * (4 * NB * lg + 4 * j));
+        if constexpr (EPI == EPI_RESID) gv[j] = *reinterpret_cast<const f32x4 *>(epi + 256 + 4 * (4 * NB * lg + 4 * j));
+      }
+      const int nc = en0 + 4 * NB * lg;
+      // the residual update keeps the z pieces of three batches of two row blocks in flight, in the
+      // registers the fragments leave free: stores count in vmcnt, so a load issued behind them waits
+      // for them too (a batch at a time cost one memory round trip each: 35 us on a 256 x 256 tile)
+      constexpr int ZR = EPI == EPI_RESID ? 2 : 1, ZS = 3;
+      static_assert(MB % ZR == 0, "row blocks per batch");
+      f32x4 z[ZS][ZR][NB];
+      auto ld_z = [&](int set, int i0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < ZR; ++i) {
+          const int rl = wm * (BM / 2) + 16 * (i0 + i) + lr;
+          const float *zr = p.z + size_t(etr.row0 + min(rl, etr.nrows - 1)) * p.ldz;
+#pragma unroll
+          for (int j = 0; j < NB; ++j) z[set][i][j] = *reinterpret_cast<const f32x4 *>(zr + min(nc + 4 * j, p.N - 4));
+        }
+      };
+      if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+        for (int s = 0; s < ZS; ++s)
+          if (s * ZR < MB) ld_z(s, s * ZR);
+      }
+#pragma unroll
+      for (int i0 = 0; i0 < MB; i0 += ZR) {
+#pragma unroll
+        for (int ii = 0; ii < ZR; ++ii) {
+          const int i = i0 + ii, rl = wm * (BM / 2) + 16 * i + lr;
+          if (rl < etr.nrows) {
+            const size_t m = size_t(etr.row0 + rl);
+            uint2 o[NB];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+              float v[4] = {acc[i][j][0] + __uint_as_float(bu[j].x << 16), acc[i][j][1] + __uint_as_float(bu[j].x & 0xffff0000u),
+                            acc[i][j][2] + __uint_as_float(bu[j].y << 16), acc[i][j][3] + __uint_as_float(bu[j].y & 0xffff0000u)};
+              if constexpr (EPI == EPI_RESID) {
+                f32x4 zn = z[i0 / ZR % ZS][ii][j];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) zn[e] += gv[j][e] * v[e];
+                if (nc + 4 * j < p.N) *reinterpret_cast<f32x4 *>(p.z + m * p.ldz + nc + 4 * j) = zn;
+              } else {
+                if constexpr (EPI == EPI_GELU) {
+#pragma unroll
+                  for (int e = 0; e < 4; ++e) v[e] = gelu_tanh(v[e]);
+                }
+                o[j] = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+              }
+            }
+            if constexpr (EPI != EPI_RESID) {
+              uint16_t *op = reinterpret_cast<uint16_t *>(p.out) + m * p.ldo + nc;
+#pragma unroll
+              for (int j = 0; j < NB; ++j)
+                if (nc + 4 * j < p.N) *reinterpret_cast<uint2 *>(op + 4 * j) = o[j];
+            }
+          }
+        }
+        asm volatile("" ::: "memory");  // the next blocks' operands stay below these stores
+        if constexpr (EPI == EPI_RESID) {
+          if (i0 + ZS * ZR < MB) ld_z(i0 / ZR % ZS, i0 + ZS * ZR);
+        }
+      }
+    } else {
+      float *slot = cur.slot;
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) *reinterpret_cast<f32x4 *>(slot + T::part_index(wid, i, j, lane)) = acc[i][j];
+    }
+    cur = uni(sk_next_item(cc, q, rg, pid, p.part, T::kPartFloats));
+    if (!cur.valid) break;
+  }
+  wait_vm<0>();
+}
+
+// The tile of a projection, chosen on the device (only it knows the row counts; the main kernel and the
+// fixup derive the same one): the shorter of two estimates in units of 10 ns, from measured rounds.  A
+// K step takes 1.46 us on a 256 x 256 tile and 0.91 on 192 x 192; a tile adds its prologue and epilogue,
+// 7 and 4 us, or 43 and 16 where it updates z (every workgroup reads and writes its tile's z at once, at
+// the copy rate).  A plan that cuts tiles spreads the K steps evenly and adds its partials and their
+// fixup, about 30 and 20 us.  2766 rows of a 64 x 64 grid: 192 x 192 for all four projections (QKV 151 us
+// against 168, output 69 / 115, MLP up 196 / 198, MLP down 191 / 225); 25000 rows in 8 samples: 256 x 256
+// (QKV 1208 against 1256, MLP up 1535 / 1660, MLP down 1640 / 1675) but for the output (561 / 553).
+template <int EPI>
+HILO_DEV uint32_t plan_cost(const SkPlan &q, int step, int tile, int tile_z, int cut) {
+  constexpr uint32_t P = kGemmWorkgroups;
+  const uint32_t rounds = (uint32_t(q.T) + P - 1) / P, t = EPI == EPI_RESID ? tile_z : tile;
+  if (q.s == 1 && q.I == 0) return rounds * (q.nk * step + t);
+  return uint32_t(q.T) * q.nk / P * step + rounds * t + cut;
+}
+
+template <int EPI>
+HILO_DEV bool tile_256(const GemmProblem &p, SkPlan &q) {
+  const SkPlan q2 = sk_plan(p, 256, 256);
+  q = sk_plan(p, 192, 192);
+  if (plan_cost<EPI>(q2, 146, 700, 4300, 3000) >= plan_cost<EPI>(q, 91, 400, 1600, 2000)) return false;
+  q = q2;
+  return true;
+}
+
+template <int EPI, int ROLE>
+__global__ __launch_bounds__(512, 2) void k_gemm8(GemmProblem p) {
+  constexpr int L0 = g8::Geo<192, 192>::LDS, L1 = g8::Geo<256, 256>::LDS;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[L0 > L1 ? L0 : L1];
+  const int pid = xcd_remap(blockIdx.x, kGemmWorkgroups);
+  SkPlan q;
+  if (tile_256<EPI>(p, q)) gemm8_run<256, 256, EPI>(p, q, pid, lds);
+  else gemm8_run<192, 192, EPI>(p, q, pid, lds);
 }
 
 // Finishes every tile left in partials.  A work item is one fragment row of one main-kernel wave
@@ -1021,11 +1351,12 @@ __global__ __launch_bounds__(256) void k_gemm_big(GemmProblem p) {
 constexpr int kFixThreads = 256;
 constexpr int kFixBatch = 4;
 
-template <int BM, int BN, int WM, int WN, int EPI, int ROLE, bool F8 = false>
-__global__ __launch_bounds__(kFixThreads) void k_gemm_fix(GemmProblem p, int P) {
-  using T = SkTile<BM, BN, WM, WN>;
+template <int BM, int BN, int WM, int WN, bool CONTIG, int EPI, bool F8>
+HILO_DEV void gemm_fix(const GemmProblem &p, const SkPlan &q) {
+  constexpr int P = kGemmWorkgroups;
+  if (q.s == 1 && q.I == 0) return;  // every tile was finished by the main kernel
+  using T = SkTile<BM, BN, WM, WN, CONTIG>;
   constexpr int TM = T::TM, TN = T::TN, NW = T::NW, FW = kFixThreads / 64;
-  const SkPlan q = sk_plan(p, BM, BN, P, F8 ? 128 : 64);
   const int nfix = q.s > 1 ? q.T : q.U - q.dp;
   const int lane = threadIdx.x & 63;
   const int items = nfix * NW * TM;
@@ -1103,6 +1434,18 @@ __global__ __launch_bounds__(kFixThreads) void k_gemm_fix(GemmProblem p, int P) 
     }
     T::template epilogue_rows<EPI, 1, F8>(p, tr, tn * BN, wid, i, lane, acc);
   }
+}
+
+template <int BM, int BN, int EPI, int ROLE>
+__global__ __launch_bounds__(kFixThreads) void k_gemm_fix(GemmProblem p) {
+  gemm_fix<BM, BN, 2, 2, false, EPI, true>(p, sk_plan(p, BM, BN, 128));
+}
+
+template <int EPI, int ROLE>
+__global__ __launch_bounds__(kFixThreads) void k_gemm8_fix(GemmProblem p) {
+  SkPlan q;
+  if (tile_256<EPI>(p, q)) gemm_fix<256, 256, 2, 4, true, EPI, false>(p, q);
+  else gemm_fix<192, 192, 2, 4, true, EPI, false>(p, q);
 }
 
 // ------------------------------------------------------------------------------- fp32 path
@@ -1190,25 +1533,11 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmProblem p) {
 
 // ------------------------------------------------------------------------------- dispatch
 
-// CUs of the current device (cached per device).
-int device_cus() {
-  static int ncu[64] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-  if (ncu[dev] == 0) {
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-      n = kBigMaxWorkgroups;
-    ncu[dev] = n;
-  }
-  return ncu[dev];
-}
-
 // BM x BN tiles: one persistent workgroup per CU.
 template <int BM, int BN, int ROLE, bool F8 = false>
 static hipError_t run_big(const GemmProblem &p, hipStream_t st) {
-  static_assert(size_t(BM) * BN * 3 * kBigMaxWorkgroups * sizeof(float) <= kSkPartBytes, "partial area too small");
-  const int P = device_cus() < kBigMaxWorkgroups ? device_cus() : kBigMaxWorkgroups;
+  static_assert(size_t(BM) * BN * 3 * kGemmWorkgroups * sizeof(float) <= kSkPartBytes, "partial area too small");
+  constexpr int P = kGemmWorkgroups;
   hipLaunchKernelGGL((k_gemm_big<BM, BN, role_epilogue(ROLE), ROLE, F8>), dim3(P), dim3(256), 0, st, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1218,7 +1547,21 @@ static hipError_t run_big(const GemmProblem &p, hipStream_t st) {
   if (tiles_max < P && !long_k) return hipSuccess;
   // P workgroups stride over the fixup's items: few enough that a launch with nothing to finish
   // (the device's row counts led to whole tiles) costs little
-  hipLaunchKernelGGL((k_gemm_fix<BM, BN, 2, 2, role_epilogue(ROLE), ROLE, F8>), dim3(P), dim3(kFixThreads), 0, st, p, P);
+  hipLaunchKernelGGL((k_gemm_fix<BM, BN, role_epilogue(ROLE), ROLE>), dim3(P), dim3(kFixThreads), 0, st, p);
+  return hipGetLastError();
+}
+
+// bf16: one persistent workgroup per CU, the tile chosen on the device.
+template <int ROLE>
+static hipError_t run_bf16(const GemmProblem &p, hipStream_t st) {
+  constexpr int P = kGemmWorkgroups;
+  hipLaunchKernelGGL((k_gemm8<role_epilogue(ROLE), ROLE>), dim3(P), dim3(512), 0, st, p);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  // no tile is ever cut when even 192 x 192 tiles are fewer than workgroups and K is short
+  const long long tiles_max = (long long)p.B * ((p.max_img_rows + 191) / 192 + (p.L + 191) / 192) * ((p.N + 191) / 192);
+  if (tiles_max < P && p.K / 64 <= kNoSplitSteps) return hipSuccess;
+  hipLaunchKernelGGL((k_gemm8_fix<role_epilogue(ROLE), ROLE>), dim3(P), dim3(kFixThreads), 0, st, p);
   return hipGetLastError();
 }
 
@@ -1246,10 +1589,10 @@ hipError_t launch_gemm(bool bf16, int role, const GemmProblem &p, hipStream_t st
   // QKV took 178 us as two launches (256 x 256, then 256 x 192 for the columns one wave could not
   // hold) against 161, MLP up 230 us as two waves plus a stream-K tail against 218.
   switch (role) {
-    case GEMM_QKV: return run_big<192, 192, GEMM_QKV>(p, st);
-    case GEMM_O: return run_big<192, 192, GEMM_O>(p, st);
-    case GEMM_FC1: return run_big<192, 192, GEMM_FC1>(p, st);
-    default: return run_big<192, 192, GEMM_FC2>(p, st);
+    case GEMM_QKV: return run_bf16<GEMM_QKV>(p, st);
+    case GEMM_O: return run_bf16<GEMM_O>(p, st);
+    case GEMM_FC1: return run_bf16<GEMM_FC1>(p, st);
+    default: return run_bf16<GEMM_FC2>(p, st);
   }
 }
 

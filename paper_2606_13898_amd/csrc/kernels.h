@@ -87,9 +87,9 @@ struct GemmProblem {
 
 // Partial-sum area of the GEMMs (part of the caller's workspace): one slot per data-parallel unit
 // of a split wave plus two per workgroup for its stream-K range, one fp32 256 x 256 tile per slot,
-// one workgroup per CU (at most 256).
-constexpr int kBigMaxWorkgroups = 256;
-constexpr size_t kSkPartBytes = size_t(kBigMaxWorkgroups) * 3 * 256 * 256 * sizeof(float);
+// one workgroup per CU (256; no workgroup waits for another, so fewer CUs would do).
+constexpr int kGemmWorkgroups = 256;
+constexpr size_t kSkPartBytes = size_t(kGemmWorkgroups) * 3 * 256 * 256 * sizeof(float);
 hipError_t launch_gemm(bool bf16, int role, const GemmProblem &p, hipStream_t st);
 // FP8 E4M3 operands (A [Tmax][K] codes, W[s] [N][K] codes, per-row scales), bf16 bias; the
 // epilogue of the role (bf16 output or the float32 residual update); K % 128 == 0, N % 16 == 0.

@@ -29,8 +29,8 @@ def test_attention_core_f32(hd, lens, heads):
     assert_close(to_np(out), O.attention_core(qkv, cu, heads), "f32", "float32 attention core")
 
 
-def run_mlp(shape, lens, seed):
-    """hilo_mlp on packed rows of the given sample lengths -> (z after, oracle's z)."""
+def run_mlp(shape, lens, seed, rows=None):
+    """hilo_mlp on packed rows of the given sample lengths -> (z after, oracle's z), for `rows` if given."""
     rng = np.random.default_rng(seed)
     cu, D = _cu(lens), shape.dim
     z = rng.standard_normal((int(cu[-1]), D)).astype(np.float32)
@@ -43,8 +43,8 @@ def run_mlp(shape, lens, seed):
     ws = torch.empty(hilo.hilo_workspace_bytes(sh), dtype=torch.uint8, device="cuda")
     hilo.hilo_mlp(sh, zd, torch.from_numpy(cu).cuda(), hilo.mlp_weights(dev), torch.from_numpy(mod).cuda(), ws)
     torch.cuda.synchronize()
-    want = O.mlp(z.astype(np.float64), np.arange(int(cu[-1])), cu, shape.text_len, w, mod)
-    return to_np(zd), want
+    rows = np.arange(int(cu[-1])) if rows is None else rows
+    return to_np(zd)[rows], O.mlp(z[rows].astype(np.float64), rows, cu, shape.text_len, w, mod)
 
 
 # 32 x 32 tiles, K split over 4 waves in steps of 16 (D 64: one step per wave; 192: three, less than
@@ -56,3 +56,18 @@ def test_mlp_f32(dim, mlp, lens, text):
     shape = inputs.BlockShape(len(lens), 1, 2, 2 * ((max(lens) + 3) // 4), text, dim, dim // 64, 64, mlp, "f32")
     got, want = run_mlp(shape, lens, 3)
     assert_close(got, want, "f32", "float32 MLP")
+
+
+# the bf16 projections choose 256 x 256 or 192 x 192 tiles from the row counts (tests/
+# test_gemm_schedule.py models the plans).  One K step per tile, N below a tile, row tails; 256 whole
+# 256 x 256 tiles, then 12 of 192 x 192 cut into 22 pieces and a stream-K tail; 1040 tiles of 256 x 256
+# in four whole waves and a stream-K tail that cuts 16
+@pytest.mark.parametrize("dim,mlp,lens,text", [(64, 320, [193, 65], 31), (512, 16384, [600], 40),
+                                               (2048, 13312, [5100], 0)])
+def test_mlp_bf16(dim, mlp, lens, text):
+    print(f"[kernel] bf16 MLP dim={dim} mlp={mlp} lens={lens} text={text}", flush=True)
+    shape = inputs.BlockShape(len(lens), 1, 2, 2 * ((max(lens) + 3) // 4), text, dim, dim // 64, 64, mlp, "bf16")
+    T = sum(lens)
+    rows = None if T < 1000 else np.sort(np.random.default_rng(5).choice(T, 160, replace=False))
+    got, want = run_mlp(shape, lens, 4, rows)
+    assert_close(got, want, "bf16", "bf16 MLP")
