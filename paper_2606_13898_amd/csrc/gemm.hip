@@ -146,20 +146,27 @@ constexpr int kNoSplitSteps = 64;
 // at 256 x 256) that the fixup reads back, so a short tail goes to fewer workgroups.
 constexpr int kSkMinSteps = 12;
 
-HILO_DEV SkPlan sk_plan(const GemmProblem &p, int BM, int BN, int kstep = 64) {
+// Whether T tiles of nk K steps run whole.
+HILO_DEV bool runs_whole(int T, int nk) {
+  constexpr int P = kGemmWorkgroups;
+  // a stream-K tail costs a partial tile (144 or 256 KiB) per piece; when the last wave holds at
+  // least half of P tiles, whole tiles in ceil(T / P) waves finish sooner
+  const bool whole_waves = T >= P && (T % P == 0 || 2 * (T % P) >= P);
+  // a single wave that fills at least 7/8 of the workgroups also runs whole tiles (cutting K would
+  // add a partial per tile to save at most an eighth)
+  const bool full_wave = T < P && 8 * T >= 7 * P;
+  return (T < P && nk <= kNoSplitSteps) || whole_waves || full_wave;
+}
+
+// The plan of R row tiles of the problem on BN-column tiles.
+HILO_DEV SkPlan sk_plan(const GemmProblem &p, int R, int BN, int kstep = 64) {
   constexpr int P = kGemmWorkgroups;
   SkPlan q;
-  q.R = row_tiles_total(p, BM);
+  q.R = R;
   q.TN = (p.N + BN - 1) / BN;
   q.T = q.R * q.TN;
   q.nk = p.K / kstep;
-  // a stream-K tail costs a partial tile (144 or 256 KiB) per piece; when the last wave holds at
-  // least half of P tiles, whole tiles in ceil(T / P) waves finish sooner
-  const bool whole_waves = q.T >= P && 2 * (q.T % P) >= P;
-  // a single wave that fills at least 7/8 of the workgroups also runs whole tiles (cutting K would
-  // add a partial per tile to save at most an eighth)
-  const bool full_wave = q.T < P && 8 * q.T >= 7 * P;
-  if ((q.T < P && q.nk <= kNoSplitSteps) || whole_waves || full_wave) {
+  if (runs_whole(q.T, q.nk)) {
     q.s = 1;
     q.U = q.dp = q.T;
     q.len = q.nk;
@@ -716,7 +723,7 @@ __global__ __launch_bounds__(256) void k_gemm_big(GemmProblem p) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[G::LDS];
 
   const int pid = xcd_remap(blockIdx.x, kGemmWorkgroups);
-  const SkPlan q = sk_plan(p, BM, BN, F8 ? 128 : 64);
+  const SkPlan q = sk_plan(p, row_tiles_total(p, BM), BN, F8 ? 128 : 64);
   const SkRange rg = sk_range(q, pid);
 
   const int lane = threadIdx.x & 63;
@@ -1308,29 +1315,136 @@ HILO_DEV void gemm8_run(const GemmProblem &p, const SkPlan &q, int pid, uint8_t 
   wait_vm<0>();
 }
 
+// Small problems: 64 x 32 tiles, four waves each (a workgroup holds two), K split over the four in steps of
+// 64 and their sums added through LDS.  Fragments come straight from global memory: lane (lr, lg) takes
+// the 32 bytes at 32 lg of a row's 128-byte K step, two chunks for two MFMAs (any order of K will do as
+// long as both operands agree).  What bounds it is the latency of one tile, about 3 us plus 1.2 us per
+// 256 of K, or 2.7 where both tiles are busy (12 KB of fragments per step and wave at the L2-to-CU rate), so it is the better plan where
+// 192 x 192 tiles would leave most CUs idle for a long K: 2 x ~320 rows, D 256, MLP 1024: QKV 14.4 -> 9.1
+// us by event pairs, output 20.6 -> 8.1, MLP up 17.2 -> 9.7, MLP down 28.6 -> 12.1; at 704 rows, D 1024, it
+// still wins for the output (34.5 -> 18 us) and MLP down (73 -> 49), and loses for QKV (26 against 36).
+template <int EPI>
+HILO_DEV void gemm_small_run(const GemmProblem &p, int rows, int pid, uint8_t *lds) {
+  constexpr int BM = 64, BN = 32, MB = 4, NB = 2;
+  f32x4 *part = reinterpret_cast<f32x4 *>(lds);  // [2 tiles][4 waves][8 blocks][64 lanes]
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wid & 3;
+  const int lr = lane & 15, lg = lane >> 4;
+  const int tilesN = p.N / BN, tiles = rows * tilesN;  // N % 64 == 0
+  const int steps = p.K / 64, s0 = steps * w / 4, s1 = steps * (w + 1) / 4;
+  for (int t0 = pid; t0 < tiles; t0 += 2 * kGemmWorkgroups) {  // the same number of turns for both tiles
+    const int t = t0 + (wid >> 2) * kGemmWorkgroups;
+    const bool on = t < tiles;
+    const int tn = on ? t % tilesN : 0, n0 = tn * BN;
+    const TileRows tr = uni(decode_row_tile(p, BM, on ? t / tilesN : 0));
+    const char *A[MB], *W[NB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+      A[i] = reinterpret_cast<const char *>(p.A) + (size_t(tr.row0 + min(16 * i + lr, tr.nrows - 1)) * p.lda) * 2 + 32 * lg;
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      W[j] = reinterpret_cast<const char *>(tr.sigma ? p.W[1] : p.W[0]) + (size_t(n0 + 16 * j + lr) * p.K) * 2 + 32 * lg;
+    f32x4 acc[MB][NB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto load = [&](int s, bf16x8 (&a)[2][MB], bf16x8 (&b)[2][NB]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i) a[h][i] = *reinterpret_cast<const bf16x8 *>(A[i] + size_t(s) * 128 + 16 * h);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) b[h][j] = *reinterpret_cast<const bf16x8 *>(W[j] + size_t(s) * 128 + 16 * h);
+      }
+    };
+    auto mul = [&](const bf16x8 (&a)[2][MB], const bf16x8 (&b)[2][NB]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[h][j], a[h][i], acc[i][j], 0, 0, 0);
+    };
+    if (on && s0 < s1) {
+      bf16x8 xa[2][MB], xb[2][NB], ya[2][MB], yb[2][NB];
+      load(s0, xa, xb);
+#pragma unroll 1
+      for (int s = s0; s < s1; s += 2) {
+        if (s + 1 < s1) load(s + 1, ya, yb);
+        mul(xa, xb);
+        if (s + 1 >= s1) break;
+        if (s + 2 < s1) load(s + 2, xa, xb);
+        mul(ya, yb);
+      }
+    }
+    f32x4 *mine = part + (wid * MB * NB) * 64 + lane;
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) mine[(i * NB + j) * 64] = acc[i][j];
+    __syncthreads();
+    // wave w finishes row block w: rows 16 w + lr, columns 16 j + 4 lg .. + 3
+    if (on && 16 * w + lr < tr.nrows) {
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const f32x4 *src = part + ((wid & 4) * MB * NB + w * NB + j) * 64 + lane;
+        const f32x4 v = (src[0] + src[MB * NB * 64]) + (src[2 * MB * NB * 64] + src[3 * MB * NB * 64]);
+        const float o[4] = {v[0], v[1], v[2], v[3]};
+        epilogue4<EPI, true>(p, tr, tr.row0 + 16 * w + lr, n0 + 16 * j + 4 * lg, o);
+      }
+    }
+    __syncthreads();  // the next tiles' sums go to the same LDS
+  }
+}
+
 // The tile of a projection, chosen on the device (only it knows the row counts; the main kernel and the
 // fixup derive the same one): the shorter of two estimates in units of 10 ns, from measured rounds.  A
 // K step takes 1.46 us on a 256 x 256 tile and 0.91 on 192 x 192; a tile adds its prologue and epilogue,
 // 7 and 4 us, or 43 and 16 where it updates z (every workgroup reads and writes its tile's z at once, at
 // the copy rate).  A plan that cuts tiles spreads the K steps evenly and adds its partials and their
-// fixup, about 30 and 20 us.  2766 rows of a 64 x 64 grid: 192 x 192 for all four projections (QKV 151 us
+// fixup, about 30 and 20 us; a turn of TILE_SMALL is described at gemm_small_run.  2766 rows of a 64 x 64 grid: 192 x 192 for all four projections (QKV 151 us
 // against 168, output 69 / 115, MLP up 196 / 198, MLP down 191 / 225); 25000 rows in 8 samples: 256 x 256
 // (QKV 1208 against 1256, MLP up 1535 / 1660, MLP down 1640 / 1675) but for the output (561 / 553).
 template <int EPI>
-HILO_DEV uint32_t plan_cost(const SkPlan &q, int step, int tile, int tile_z, int cut) {
+HILO_DEV uint32_t plan_cost(uint32_t T, uint32_t nk, uint32_t step, uint32_t tile, uint32_t tile_z, uint32_t cut) {
   constexpr uint32_t P = kGemmWorkgroups;
-  const uint32_t rounds = (uint32_t(q.T) + P - 1) / P, t = EPI == EPI_RESID ? tile_z : tile;
-  if (q.s == 1 && q.I == 0) return rounds * (q.nk * step + t);
-  return uint32_t(q.T) * q.nk / P * step + rounds * t + cut;
+  const uint32_t rounds = (T + P - 1) / P, t = EPI == EPI_RESID ? tile_z : tile;
+  return runs_whole(T, nk) ? rounds * (nk * step + t) : T * nk / P * step + rounds * t + cut;
 }
 
+enum Tile { TILE_192, TILE_256, TILE_SMALL };
+
+// The tile and its row tiles.  Nothing here divides by a value that is not a constant: every launch
+// waits for this, about 2 us when it formed the three plans instead.
 template <int EPI>
-HILO_DEV bool tile_256(const GemmProblem &p, SkPlan &q) {
-  const SkPlan q2 = sk_plan(p, 256, 256);
-  q = sk_plan(p, 192, 192);
-  if (plan_cost<EPI>(q2, 146, 700, 4300, 3000) >= plan_cost<EPI>(q, 91, 400, 1600, 2000)) return false;
-  q = q2;
-  return true;
+HILO_DEV Tile choose_tile(const GemmProblem &p, int &rows) {
+  constexpr uint32_t P = kGemmWorkgroups;
+  int r64 = 0, r192 = 0, r256 = 0;
+  for (int s = 0; s < p.B; ++s) {
+    const int img = cu_at(p.cu, s + 1) - p.L - cu_at(p.cu, s);
+    r64 += (img + 63) / 64 + (p.L + 63) / 64;
+    r192 += (img + 191) / 192 + (p.L + 191) / 192;
+    r256 += (img + 255) / 256 + (p.L + 255) / 256;
+  }
+  const uint32_t nk = p.K / 64, tiles = uint32_t(r64) * (p.N / 32);
+  uint32_t best = plan_cost<EPI>(r192 * ((p.N + 191) / 192), nk, 91, 400, 1600, 2000);
+  rows = r192;
+  Tile t = TILE_192;
+  const uint32_t c256 = plan_cost<EPI>(r256 * ((p.N + 255) / 256), nk, 146, 700, 4300, 3000);
+  if (c256 < best) {
+    best = c256;
+    rows = r256;
+    t = TILE_256;
+  }
+  // a turn takes 2 tiles a workgroup; with one the K steps run twice as fast
+  const uint32_t turns = (tiles + 2 * P - 1) / (2 * P);
+  if (turns * ((nk + 3) / 4 * (tiles <= P ? 120 : 270) + 300) < best) {
+    rows = r64;
+    t = TILE_SMALL;
+  }
+  return t;
 }
 
 template <int EPI, int ROLE>
@@ -1338,9 +1452,12 @@ __global__ __launch_bounds__(512, 2) void k_gemm8(GemmProblem p) {
   constexpr int L0 = g8::Geo<192, 192>::LDS, L1 = g8::Geo<256, 256>::LDS;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[L0 > L1 ? L0 : L1];
   const int pid = xcd_remap(blockIdx.x, kGemmWorkgroups);
-  SkPlan q;
-  if (tile_256<EPI>(p, q)) gemm8_run<256, 256, EPI>(p, q, pid, lds);
-  else gemm8_run<192, 192, EPI>(p, q, pid, lds);
+  int rows;
+  switch (choose_tile<EPI>(p, rows)) {
+    case TILE_SMALL: gemm_small_run<EPI>(p, rows, pid, lds); break;
+    case TILE_256: gemm8_run<256, 256, EPI>(p, sk_plan(p, rows, 256), pid, lds); break;
+    default: gemm8_run<192, 192, EPI>(p, sk_plan(p, rows, 192), pid, lds);
+  }
 }
 
 // Finishes every tile left in partials.  A work item is one fragment row of one main-kernel wave
@@ -1438,14 +1555,15 @@ HILO_DEV void gemm_fix(const GemmProblem &p, const SkPlan &q) {
 
 template <int BM, int BN, int EPI, int ROLE>
 __global__ __launch_bounds__(kFixThreads) void k_gemm_fix(GemmProblem p) {
-  gemm_fix<BM, BN, 2, 2, false, EPI, true>(p, sk_plan(p, BM, BN, 128));
+  gemm_fix<BM, BN, 2, 2, false, EPI, true>(p, sk_plan(p, row_tiles_total(p, BM), BN, 128));
 }
 
 template <int EPI, int ROLE>
 __global__ __launch_bounds__(kFixThreads) void k_gemm8_fix(GemmProblem p) {
-  SkPlan q;
-  if (tile_256<EPI>(p, q)) gemm_fix<256, 256, 2, 4, true, EPI, false>(p, q);
-  else gemm_fix<192, 192, 2, 4, true, EPI, false>(p, q);
+  int rows;
+  const Tile t = choose_tile<EPI>(p, rows);
+  if (t == TILE_256) gemm_fix<256, 256, 2, 4, true, EPI, false>(p, sk_plan(p, rows, 256));
+  else if (t == TILE_192) gemm_fix<192, 192, 2, 4, true, EPI, false>(p, sk_plan(p, rows, 192));
 }
 
 // ------------------------------------------------------------------------------- fp32 path

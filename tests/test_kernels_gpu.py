@@ -58,16 +58,18 @@ def test_mlp_f32(dim, mlp, lens, text):
     assert_close(got, want, "f32", "float32 MLP")
 
 
-# the bf16 projections choose 256 x 256 or 192 x 192 tiles from the row counts (tests/
-# test_gemm_schedule.py models the plans).  One K step per tile, N below a tile, row tails; 256 whole
-# 256 x 256 tiles, then 12 of 192 x 192 cut into 22 pieces and a stream-K tail; 1040 tiles of 256 x 256
-# in four whole waves and a stream-K tail that cuts 16
-@pytest.mark.parametrize("dim,mlp,lens,text", [(64, 320, [193, 65], 31), (512, 16384, [600], 40),
+# the bf16 projections choose their tile from the row counts (tests/test_gemm_schedule.py models the
+# plans of the large ones).  Small tiles: K of one, three and five steps over four waves, row tails, more
+# tiles than workgroups; 192 x 192 tiles of one K step, N below a tile; 256 whole 256 x 256 tiles, then
+# 12 of 192 x 192 cut into 22 pieces and a stream-K tail; 1040 tiles of 256 x 256 in four whole waves
+# and a stream-K tail that cuts 16
+@pytest.mark.parametrize("dim,mlp,lens,text", [(64, 320, [193, 65], 31), (192, 960, [705, 64, 1], 0),
+                                               (64, 320, [1100, 901], 31), (512, 16384, [600], 40),
                                                (2048, 13312, [5100], 0)])
 def test_mlp_bf16(dim, mlp, lens, text):
     print(f"[kernel] bf16 MLP dim={dim} mlp={mlp} lens={lens} text={text}", flush=True)
     shape = inputs.BlockShape(len(lens), 1, 2, 2 * ((max(lens) + 3) // 4), text, dim, dim // 64, 64, mlp, "bf16")
     T = sum(lens)
-    rows = None if T < 1000 else np.sort(np.random.default_rng(5).choice(T, 160, replace=False))
+    rows = None if T < 2500 and dim < 512 else np.sort(np.random.default_rng(5).choice(T, 160, replace=False))
     got, want = run_mlp(shape, lens, 4, rows)
     assert_close(got, want, "bf16", "bf16 MLP")
