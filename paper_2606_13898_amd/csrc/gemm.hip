@@ -7,9 +7,8 @@
 // bf16 path (k_gemm8): one persistent workgroup of 8 waves per CU, 256 x 256 or 192 x 192 tiles (chosen
 // on the device from the row counts), K through LDS in 128-byte windows filled by direct global->LDS
 // loads, fragments read half a window ahead of their MFMAs.
-// FP8 path (k_gemm_big): one persistent workgroup of 4 waves per CU, 192 x 192 tiles, or 256 x 256 for
-// the QKV projection (which writes FP8 q / k with one scale per row and head: a wave's 128 columns hold
-// whole heads), v_mfma_f32_32x32x64_f8f6f4 on E4M3 codes, fp32 accumulators in AGPRs.
+// FP8 path (k_gemm8_fp8): the same loop on E4M3 codes, 192 x 192 tiles, or 256 x 256 for the QKV projection
+// (which writes FP8 q / k with one scale per row and head: a wave's 128 columns hold whole heads).
 // Both: whole data-parallel waves of tiles run first, then a stream-K remainder; cut tiles leave fp32
 // partials that a fixup kernel adds in a fixed order before the epilogue.
 // float32 path: v_mfma_f32_16x16x4_f32 straight from global memory, K split over a workgroup's waves.
@@ -277,7 +276,7 @@ struct SkTile {
     return ((size_t(wid) * TM * TN + i * TN + j) * 64 + lane) * 4;
   }
 
-  // The FP8 q / k codes of fragment row i0 of wave wid (the whole-tile form is big_epilogue_qk8):
+  // The FP8 q / k codes of fragment row i0 of wave wid (the whole-tile form is epilogue32_qk8):
   // the wave's BN / WN columns hold whole heads; a row's columns of one head are spread over the 4
   // lanes l % 16 + 16 m, each holding 4 columns of every 16.
   HILO_DEV static void epilogue_rows_qk8(const GemmProblem &p, const TileRows &tr, int n0, int wid, int i0,
@@ -407,37 +406,6 @@ struct SkTile {
   }
 };
 
-// ------------------------------------------------------------------------------ MFMA tiles
-//
-// One persistent workgroup per CU, 4 waves (2 x 2).  For 256 x 256 tiles the wave tile is 128 x 128
-// as 4 x 4 blocks of 32 x 32: 256 fp32 accumulators per lane, held in AGPRs, and per K step the CU
-// loads half the operand bytes per FLOP of a 128 x 128 tile (BM x BN tiles: BM/64 x BN/64 blocks per
-// wave, the same schedule).  K runs in stages of 64 bytes per row (32 bf16 or 64 FP8 values)
-// through a 4-slot LDS ring (32 KiB per 256 x 256 stage: the stage's A rows, then its W rows, 16-byte
-// chunks swizzled), loaded by direct global->LDS loads three stages ahead (window mode, below: the
-// LDS holds three 128-byte K-step windows per row, loaded two K steps ahead).  A 256 x 256 stage is
-// 16 blocks:
-//   * bf16: two v_mfma_f32_32x32x16_bf16 per block, one per K half (chunks {h, h + 2});
-//   * FP8:  one v_mfma_f32_32x32x64_f8f6f4 per block (all four chunks, 8 registers per operand).
-// Either way lane (r, g) = (l % 32, l / 32) of a fragment reads chunks 2 g and 2 g + 1 of row r of a
-// 32-row fragment: each half-wave reads one chunk of 32 consecutive rows, which the swizzle spreads
-// over all banks (the 16 x 16 fragment order, 16 rows of two chunks per half-wave, measured 2-way
-// bank conflicts on every read).  With one wave per SIMD nothing hides a stall of the wave, so the
-// loop is a fixed schedule (inline asm pins the order):
-//   * each block row waits only for its own fragment reads (DS reads complete in order, so an exact
-//     lgkmcnt is known at every point);
-//   * before block 4 the wave waits for its loads of the *next* stage and meets the others at the
-//     barrier, which also tells it that every wave has finished reading the slot it is about to
-//     refill;
-//   * after each of blocks 4..11: one of the stage's 8 loads (three stages ahead) and two of the 16
-//     fragment reads of the next stage.
-// Fragments alternate between two register sets, so a scheduling unit is two stages (the K step of
-// the stream-K plan: 64 bf16 or 128 FP8 values).  A second cursor over the workgroup's items drives
-// the loads: at the end of an item they already fetch the next item's first stages, so its
-// epilogue overlaps them.  Past the last item the loader repeats the last stage into free slots
-// (valid addresses; keeps the vmcnt arithmetic uniform).  The epilogue's per-column and per-row
-// operands (bias, FP8 scales, gate) reach LDS by a DMA issued in the item's first stage, so the
-// epilogue never waits on the prefetch loads in flight behind them.
 // Values that are the same on every lane, restated as such (the compiler otherwise keeps some of
 // the stream-K bookkeeping in VGPRs and branches on it with exec masks).
 HILO_DEV int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -449,581 +417,15 @@ HILO_DEV float *uni(float *ptr) {
 HILO_DEV SkItem uni(const SkItem &x) { return SkItem{uni(x.t), uni(x.kb), uni(x.ke), uni(x.slot), uni(int(x.valid)) != 0}; }
 HILO_DEV TileRows uni(const TileRows &x) { return TileRows{uni(x.s), uni(x.sigma), uni(x.row0), uni(x.nrows)}; }
 
-namespace big {
-constexpr int S = 4;                   // LDS ring slots
-// per wave, behind the ring: the wave's columns of bias (bf16, <= 256 B), of the FP8 weight scales
-// (float32, <= 512 B), its rows of FP8 activation scales (<= 512 B) and its columns of the residual
-// gate (float32, <= 512 B)
-constexpr int kEpiWave = 1792, kEpiBias = 0, kEpiCol = 256, kEpiRow = 768, kEpiGate = 1280;
-HILO_DEV int swz(int r) { return ((r >> 1) & 3) ^ ((r >> 3) & 1); }
-// W row read by fragment lane r.  The 32 x 32 MFMA's output row i (the W side) lands in
-// accumulator register 4 (i / 8) + i % 4 of the lanes of half (i / 4) % 2; reading W row perm_w(i)
-// there gives lane half g the columns 16 g .. 16 g + 15 in register order.  These LDS reads are
-// conflict-free like the natural order (measured; shifting the second half by 8 rows is not).
-HILO_DEV int perm_w(int r) { return ((r & 4) ? 16 : 0) + 4 * (r >> 3) + (r & 3); }
-// A BM x BN tile on 4 waves (2 x 2), wave tile BM/2 x BN/2 as NBM x NBN blocks of 32 x 32.
-template <int BM, int BN>
-struct Geo {
-  static_assert((BM == 256 && BN == 256) || (BM == 192 && BN == 192) || (BM == 256 && BN == 192),
-                "tile shapes of the MFMA kernel");
-  static constexpr int NBM = BM / 64;        // blocks per wave column (A side)
-  static constexpr int NBN = BN / 64;        // blocks per wave row (W side)
-  static constexpr int LQ = NBM + NBN;       // load instructions per wave per stage (A rows, then W rows)
-  static constexpr int NR = 2 * LQ;          // fragment reads per wave per stage
-  static constexpr int AB = BM * 64;         // bytes of a stage's A rows
-  static constexpr int SB = (BM + BN) * 64;  // bytes of a stage
-  // Window mode: when three K steps of the tile fit in LDS, each row's 128 bytes of a K step (both
-  // of its stages) stay together, so one load instruction fetches 8 whole 128-byte lines instead of
-  // 16 half lines (measured: fewer, fuller requests to the L2); three window slots keep the loads
-  // two K steps ahead.  The 256-wide tiles hold only two windows, and one K step of prefetch
-  // measured slower than the half-line ring.
-  static constexpr int WS = 3;                          // window slots
-  static constexpr int SBW = (BM + BN) * 128;           // bytes of a window
-  static constexpr bool WIN = BM == BN && WS * SBW + 4 * kEpiWave <= 160 * 1024;
-  static constexpr int LDS = WIN ? WS * SBW + 4 * kEpiWave : S * SB + 4 * kEpiWave;
-  // every load and fragment read of a stage is issued after its barrier (block NBN) and before
-  // its last block; in window mode a stage loads BM / 32 instructions of 8 rows (its wave's A rows
-  // in the first stage of a K step, its W rows in the second), the same count as LQ for BM == BN
-  static_assert(NBN + LQ <= NBM * NBN, "stage schedule does not fit the blocks");
-  static_assert(!WIN || BM / 32 == LQ, "window loads per stage");
-};
-// Chunk swizzle of a 128-byte window row: the 16-byte chunk that global chunk c of row r occupies is
-// c ^ swzw(r).  A ds_read_b128 serves 16 lanes per cycle from 64 banks; with it every 16-lane group
-// of a fragment read (16 consecutive rows, or the perm_w rows of W) hits 16 distinct bank groups.
-HILO_DEV int swzw(int r) { return ((r >> 1) & 3) ^ ((((r >> 3) ^ (r >> 4)) & 1) << 2); }
-}  // namespace big
-
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-#define HILO_MFMA16_AGPR(ACC, FB, FA) \
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(ACC) : "v"(FB), "v"(FA) : "memory")
-// first MFMA of a tile: accumulate onto zero (no separate clearing of the AGPRs)
-#define HILO_MFMA16_AGPR0(ACC, FB, FA) \
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=a"(ACC) : "v"(FB), "v"(FA) : "memory")
-// The 8-register operands have no host counterpart: the host pass (which only needs the kernel's
-// launch stub) would reject the constraint and silently drop the stub, so it sees no asm here.
-#if defined(__HIP_DEVICE_COMPILE__)
-#define HILO_MFMA8_AGPR(ACC, FB, FA) \
-  asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, %0" : "+a"(ACC) : "v"(FB), "v"(FA) : "memory")
-#define HILO_MFMA8_AGPR0(ACC, FB, FA) \
-  asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, 0" : "=a"(ACC) : "v"(FB), "v"(FA) : "memory")
-#else
-#define HILO_MFMA8_AGPR(ACC, FB, FA) ((void)0)
-#define HILO_MFMA8_AGPR0(ACC, FB, FA) ((void)0)
-#endif
-HILO_DEV u32x8 cat8(u32x4 lo, u32x4 hi) { return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7); }
-#define HILO_DS_READ16(DST, ADDR, OFF) \
-  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(DST) : "v"(ADDR), "i"(OFF) : "memory")
+typedef int i32x8 __attribute__((ext_vector_type(8)));
 
 // One 4-byte global load per lane straight into LDS: lane l lands at byte 4 l of the destination.
 HILO_DEV void g2lds4(const void *g, void *lds_wave_base) {
   __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void *)lds_wave_base, 4, 0, 0);
 }
 
-template <int N>
-HILO_DEV void wait_lgkm_le() { asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory"); }
-
-HILO_DEV void wait_lgkm_rt(int n) {  // n is a compile-time constant after unrolling
-  switch (n) {
-    case 0: wait_lgkm_le<0>(); break;   case 1: wait_lgkm_le<1>(); break;
-    case 2: wait_lgkm_le<2>(); break;   case 3: wait_lgkm_le<3>(); break;
-    case 4: wait_lgkm_le<4>(); break;   case 5: wait_lgkm_le<5>(); break;
-    case 6: wait_lgkm_le<6>(); break;   case 7: wait_lgkm_le<7>(); break;
-    case 8: wait_lgkm_le<8>(); break;   case 9: wait_lgkm_le<9>(); break;
-    case 10: wait_lgkm_le<10>(); break; case 11: wait_lgkm_le<11>(); break;
-    case 12: wait_lgkm_le<12>(); break; case 13: wait_lgkm_le<13>(); break;
-    case 14: wait_lgkm_le<14>(); break; default: wait_lgkm_le<15>(); break;
-  }
-}
-
-// Epilogue of a BM x BN tile from the AGPR accumulators of wave wid.  The W fragments are read in
-// the row order perm_w, so lane l of block (bi, bj) holds row 32 bi + l % 32 of the wave tile and, in
-// register v, column 32 bj + 16 (l / 32) + v: 16 consecutive columns, stored as two 16-byte pieces
-// (bf16) or four (float32 z).  Column operands (bias, FP8 weight scales, the gate) come from the
-// wave's LDS area `epi`, once per block column; FP8 row scales once per tile.  Bias / GELU outputs
-// are rounded to bf16, the residual update adds gate * (acc + bias) to the float32 z.  Blocks leave
-// the AGPRs one at a time.
-template <int BM, int BN, int EPI, bool F8>
-HILO_DEV void big_epilogue(const GemmProblem &p, const TileRows &tr, int n0, int wid, int lane,
-                           const uint8_t *epi, f32x16 (&acc)[BM / 64][BN / 64]) {
-  using namespace big;
-  constexpr int NBM = Geo<BM, BN>::NBM, NBN = Geo<BM, BN>::NBN;
-  const int rbase = (wid >> 1) * (BM / 2) + (lane & 31);
-  const int cl0 = 16 * (lane >> 5);              // this lane's first column within a 32-column block
-  const int cbase = n0 + (wid & 1) * (BN / 2) + cl0;
-  float sa[NBM];
-#pragma unroll
-  for (int bi = 0; bi < NBM; ++bi)
-    sa[bi] = F8 ? *reinterpret_cast<const float *>(epi + kEpiRow + 4 * (32 * bi + (lane & 31))) : 1.f;
-  // The residual update loads every z piece of the wave before it stores any: stores count in
-  // vmcnt, so a z load issued after a block's stores would wait for them too (one memory round
-  // trip per block: 16.4 us per 192 x 192 tile epilogue against 13.4-14.1 with one).
-  // Lanes outside the tile load a valid element they do not store.
-  constexpr int ZB = EPI == EPI_RESID ? NBM * NBN : 1;
-  static_assert(EPI != EPI_RESID || ZB <= 9, "the wave's z pieces are held in registers");
-  float4 zz[ZB][4];
-  if constexpr (EPI == EPI_RESID) {
-#pragma unroll
-    for (int bj = 0; bj < NBN; ++bj)
-#pragma unroll
-      for (int bi = 0; bi < NBM; ++bi) {
-        const int rl = rbase + 32 * bi, n = cbase + 32 * bj;
-        const bool in = rl < tr.nrows && n < p.N;
-        const float4 *zp =
-            reinterpret_cast<const float4 *>(p.z + size_t(tr.row0 + (in ? rl : 0)) * p.ldz + (in ? n : 0));
-#pragma unroll
-        for (int h = 0; h < 4; ++h) zz[bj * NBM + bi][h] = zp[h];
-      }
-  }
-#pragma unroll
-  for (int bj = 0; bj < NBN; ++bj) {
-    const int cl = cl0 + 32 * bj, n = cbase + 32 * bj;
-    u32x4 bu[2];
-    f32x4 cv[4], gv[4];  // FP8 weight scales and the residual gate of the lane's 16 columns
-#pragma unroll
-    for (int h = 0; h < 2; ++h) bu[h] = *reinterpret_cast<const u32x4 *>(epi + kEpiBias + 2 * cl + 16 * h);
-    if constexpr (F8) {
-#pragma unroll
-      for (int h = 0; h < 4; ++h) cv[h] = *reinterpret_cast<const f32x4 *>(epi + kEpiCol + 4 * cl + 16 * h);
-    }
-    if constexpr (EPI == EPI_RESID) {
-#pragma unroll
-      for (int h = 0; h < 4; ++h) gv[h] = *reinterpret_cast<const f32x4 *>(epi + kEpiGate + 4 * cl + 16 * h);
-    }
-#pragma unroll
-    for (int bi = 0; bi < NBM; ++bi) {
-      f32x16 blk = acc[bi][bj];  // one block out of the AGPRs at a time
-      asm volatile("" : "+v"(blk));
-      const int rl = rbase + 32 * bi;
-      if (rl < tr.nrows && n < p.N) {  // N % 16 == 0: a lane's 16 columns are all inside or all out
-        const size_t m = size_t(tr.row0 + rl);
-        float v[16];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const uint32_t w = bu[e >> 3][(e >> 1) & 3];
-          const float bias = __uint_as_float((e & 1) ? (w & 0xffff0000u) : (w << 16));
-          if constexpr (F8) v[e] = blk[e] * (sa[bi] * cv[e >> 2][e & 3]) + bias;
-          else v[e] = blk[e] + bias;
-        }
-        if constexpr (EPI == EPI_RESID) {
-          float4 *zp = reinterpret_cast<float4 *>(p.z + m * p.ldz + n);
-#pragma unroll
-          for (int h = 0; h < 4; ++h) {
-            float4 z = zz[bj * NBM + bi][h];
-            z.x += gv[h][0] * v[4 * h + 0];
-            z.y += gv[h][1] * v[4 * h + 1];
-            z.z += gv[h][2] * v[4 * h + 2];
-            z.w += gv[h][3] * v[4 * h + 3];
-            zp[h] = z;
-          }
-        } else {
-          if constexpr (EPI == EPI_GELU) {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) v[e] = gelu_tanh(v[e]);
-          }
-          uint4 *op = reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(p.out) + m * p.ldo + n);
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-            op[h] = make_uint4(pack_bf16x2(v[8 * h + 0], v[8 * h + 1]), pack_bf16x2(v[8 * h + 2], v[8 * h + 3]),
-                               pack_bf16x2(v[8 * h + 4], v[8 * h + 5]), pack_bf16x2(v[8 * h + 6], v[8 * h + 7]));
-        }
-      }
-      asm volatile("" ::: "memory");  // the next block's operands stay below these stores
-    }
-  }
-}
-
-// FP8 q and k for the attention's score product, from the QKV projection's accumulators of a
-// 256 x 256 tile of FP8 operands whose columns lie below 2 D.  The wave's 128 columns hold whole
-// heads (128 / head_dim of them); per (row, head): the values acc * (row scale * weight scale) +
-// bias (as the bf16 output would take them), their amax over the head -- this lane's 16 columns of
-// each block and those of lane l ^ 32, which holds the block's other 16 -- the power-of-two scale
-// 2^k, and the E4M3 codes of the values times 2^-k (16 bytes per lane and block); then one E8M0
-// byte 127 + k per (row, head).  The values are formed twice (amax, then codes) instead of held.
-template <int BM, int BN>
-HILO_DEV void big_epilogue_qk8(const GemmProblem &p, const TileRows &tr, int n0, int wid, int lane,
-                               const uint8_t *epi, f32x16 (&acc)[BM / 64][BN / 64]) {
-  using namespace big;
-  static_assert(BN == 256, "a wave's 128 columns hold whole heads");
-  constexpr int NBM = BM / 64, NBN = BN / 64;
-  const int hd = p.head_dim, bph = hd / 32;  // blocks per head
-  const int rbase = (wid >> 1) * (BM / 2) + (lane & 31);
-  const int cl0 = 16 * (lane >> 5);
-  const int wc0 = n0 + (wid & 1) * (BN / 2);
-  auto values = [&](int bi, int bj, float sa, float (&v)[16]) __attribute__((always_inline)) {
-    const int cl = cl0 + 32 * bj;
-    u32x4 bu[2];
-    f32x4 cv[4];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) bu[h] = *reinterpret_cast<const u32x4 *>(epi + kEpiBias + 2 * cl + 16 * h);
-#pragma unroll
-    for (int h = 0; h < 4; ++h) cv[h] = *reinterpret_cast<const f32x4 *>(epi + kEpiCol + 4 * cl + 16 * h);
-    f32x16 blk = acc[bi][bj];
-    asm volatile("" : "+v"(blk));
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const uint32_t w = bu[e >> 3][(e >> 1) & 3];
-      const float bias = __uint_as_float((e & 1) ? (w & 0xffff0000u) : (w << 16));
-      v[e] = blk[e] * (sa * cv[e >> 2][e & 3]) + bias;
-    }
-  };
-#pragma unroll
-  for (int bi = 0; bi < NBM; ++bi) {
-    const float sa = *reinterpret_cast<const float *>(epi + kEpiRow + 4 * (32 * bi + (lane & 31)));
-    float am0 = 0.f, am1 = 0.f;
-#pragma unroll
-    for (int bj = 0; bj < NBN; ++bj) {
-      float v[16];
-      values(bi, bj, sa, v);
-      float m = 0.f;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) m = fmaxf(m, fabsf(v[e]));
-      if (bj / bph == 0) am0 = fmaxf(am0, m);
-      else am1 = fmaxf(am1, m);
-    }
-    am0 = fmaxf(am0, __shfl_xor(am0, 32, 64));
-    am1 = fmaxf(am1, __shfl_xor(am1, 32, 64));
-    const int k0 = pow2_exponent(am0), k1 = pow2_exponent(am1);
-    const float i0 = pow2_inverse(k0), i1 = pow2_inverse(k1);
-    const int rl = rbase + 32 * bi;
-    if (rl < tr.nrows) {
-      uint8_t *row = p.qk8 + size_t(tr.row0 + rl) * p.ldq8;
-#pragma unroll
-      for (int bj = 0; bj < NBN; ++bj) {
-        float v[16];
-        values(bi, bj, sa, v);
-        const float s = bj / bph == 0 ? i0 : i1;
-        uint4 c;
-        c.x = fp8x4(v[0] * s, v[1] * s, v[2] * s, v[3] * s);
-        c.y = fp8x4(v[4] * s, v[5] * s, v[6] * s, v[7] * s);
-        c.z = fp8x4(v[8] * s, v[9] * s, v[10] * s, v[11] * s);
-        c.w = fp8x4(v[12] * s, v[13] * s, v[14] * s, v[15] * s);
-        *reinterpret_cast<uint4 *>(row + wc0 + cl0 + 32 * bj) = c;
-      }
-      if (lane < 32) {
-        row[2 * p.D + wc0 / hd] = uint8_t(127 + k0);
-        if (bph * 2 == NBN) row[2 * p.D + wc0 / hd + 1] = uint8_t(127 + k1);
-      }
-    }
-    asm volatile("" ::: "memory");
-  }
-}
-
-template <int BM, int BN, int EPI, int ROLE, bool F8>
-__global__ __launch_bounds__(256) void k_gemm_big(GemmProblem p) {
-  using namespace big;
-  using G = Geo<BM, BN>;
-  constexpr int NBM = G::NBM, NBN = G::NBN, LQ = G::LQ, NR = G::NR, AB = G::AB, SB = G::SB;
-  constexpr bool WIN = G::WIN;
-  constexpr int SBW = G::SBW, NLA = WIN ? 2 * NBM : NBM, NLB = WIN ? 2 * NBN : NBN;
-  using T = SkTile<BM, BN, 2, 2>;       // partial slot size and layout (16 x 16 fragment order)
-  constexpr int ESZ = F8 ? 1 : 2;       // operand bytes per element
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[G::LDS];
-
-  const int pid = xcd_remap(blockIdx.x, kGemmWorkgroups);
-  const SkPlan q = sk_plan(p, row_tiles_total(p, BM), BN, F8 ? 128 : 64);
-  const SkRange rg = sk_range(q, pid);
-
-  const int lane = threadIdx.x & 63;
-  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lrow = lane >> 2, lslot = lane & 3;
-  const uint8_t *A = reinterpret_cast<const uint8_t *>(p.A);
-
-  // ---- loader: its own cursor over this workgroup's items, three stages ahead of the MFMAs (window
-  // mode: two K steps ahead); wave wid loads rows wid BM/4 .. + BM/4 - 1 of A and wid BN/4 .. +
-  // BN/4 - 1 of W, 16 rows of 64 bytes (window mode: 8 rows of 128 bytes) per 1 KiB instruction
-  SkCursor lc{pid, rg.beg};
-  const uint8_t *la[NLA], *lb[NLB];
-  int lk = 0, lke = 0;  // next stage (window mode: K step) to load, absolute in K, and its item's end
-  auto ld_src = [&](int t) __attribute__((always_inline)) {
-    int rt, tn;
-    tile_coords(q, t, rt, tn);
-    tn = uni(tn);
-    const TileRows tr = uni(decode_row_tile(p, BM, uni(rt)));
-    const uint8_t *Wt = reinterpret_cast<const uint8_t *>(tr.sigma ? p.W[1] : p.W[0]);
-    if constexpr (WIN) {
-#pragma unroll
-      for (int i = 0; i < NLA; ++i) {
-        const int r = wid * (BM / 4) + 8 * i + (lane >> 3);
-        la[i] = A + size_t(tr.row0 + min(r, tr.nrows - 1)) * p.lda * ESZ + ((lane & 7) ^ swzw(r)) * 16;
-      }
-#pragma unroll
-      for (int i = 0; i < NLB; ++i) {
-        const int r = wid * (BN / 4) + 8 * i + (lane >> 3);
-        lb[i] = Wt + size_t(min(tn * BN + r, p.N - 1)) * p.K * ESZ + ((lane & 7) ^ swzw(r)) * 16;
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < NBM; ++i) {
-        const int r = wid * (BM / 4) + 16 * i + lrow;
-        la[i] = A + size_t(tr.row0 + min(r, tr.nrows - 1)) * p.lda * ESZ + (lslot ^ swz(r)) * 16;
-      }
-#pragma unroll
-      for (int i = 0; i < NBN; ++i) {
-        const int r = wid * (BN / 4) + 16 * i + lrow;
-        lb[i] = Wt + size_t(min(tn * BN + r, p.N - 1)) * p.K * ESZ + (lslot ^ swz(r)) * 16;
-      }
-    }
-  };
-  auto ld_advance = [&]() __attribute__((always_inline)) {
-    const SkItem x = uni(sk_next_item(lc, q, rg, pid, p.part, T::kPartFloats));
-    if (x.valid) {
-      ld_src(x.t);
-      lk = WIN ? x.kb : 2 * x.kb;
-      lke = WIN ? x.ke : 2 * x.ke;
-    } else {
-      lk = lke - 1;  // no further item: repeat the last stage
-    }
-    lk = uni(lk);
-    lke = uni(lke);
-  };
-  // load instruction j (0..LQ-1) of the current loader stage into `slot`: A rows for j < NBM
-  auto ld_one = [&](int slot, int j) __attribute__((always_inline)) {
-    const int k0 = lk * 64;  // bytes
-    if (j < NBM) g2lds16(la[j] + k0, lds + slot * SB + wid * (BM / 4) * 64 + j * 1024);
-    else g2lds16(lb[j - NBM] + k0, lds + slot * SB + AB + wid * (BN / 4) * 64 + (j - NBM) * 1024);
-  };
-  // window mode: load instruction j of half h (0: the wave's A rows, 1: its W rows) of the loader's
-  // K step into window slot `ws`
-  auto ld_win = [&](int ws, int h, int j) __attribute__((always_inline)) {
-    const int k0 = lk * 128;  // bytes
-    if (h == 0) g2lds16(la[j] + k0, lds + ws * SBW + (wid * (BM / 4) + 8 * j) * 128);
-    else g2lds16(lb[j] + k0, lds + ws * SBW + BM * 128 + (wid * (BN / 4) + 8 * j) * 128);
-  };
-
-  // ---- fragment reads: lane (r, g) = (lane % 32, lane / 32) reads chunk 2 g (low half) and 2 g + 1
-  // (high half) of row r (A) or perm_w(r) (W) of a 32-row fragment; read t of a stage (slot byte
-  // offset so) is half t % 2 of W fragment t / 2 for t < 2 NBN, then of A fragment (t - 2 NBN) / 2
-  const int r8 = lane & 31, g8 = lane >> 5, w8 = perm_w(r8);
-  const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
-  const uint32_t fa8 = lds0 + (wid >> 1) * (BM / 2) * 64, fb8 = lds0 + AB + (wid & 1) * (BN / 2) * 64;
-  const uint32_t fa8l = fa8 + r8 * 64 + (((2 * g8) ^ swz(r8)) * 16), fa8h = fa8 + r8 * 64 + (((2 * g8 + 1) ^ swz(r8)) * 16);
-  const uint32_t fb8l = fb8 + w8 * 64 + (((2 * g8) ^ swz(w8)) * 16), fb8h = fb8 + w8 * 64 + (((2 * g8 + 1) ^ swz(w8)) * 16);
-  // window mode: the same lane mapping on 128-byte rows; half h (0, 1) of a K step holds its global
-  // chunks 4 h .. 4 h + 3, and a fragment spans 32 rows of 128 bytes
-  const uint32_t wa = lds0 + (wid >> 1) * (BM / 2) * 128 + r8 * 128;
-  const uint32_t wb = lds0 + BM * 128 + (wid & 1) * (BN / 2) * 128 + w8 * 128;
-  const uint32_t fwa[4] = {wa + (((2 * g8) ^ swzw(r8)) * 16), wa + (((2 * g8 + 1) ^ swzw(r8)) * 16),
-                           wa + (((4 + 2 * g8) ^ swzw(r8)) * 16), wa + (((5 + 2 * g8) ^ swzw(r8)) * 16)};
-  const uint32_t fwb[4] = {wb + (((2 * g8) ^ swzw(w8)) * 16), wb + (((2 * g8 + 1) ^ swzw(w8)) * 16),
-                           wb + (((4 + 2 * g8) ^ swzw(w8)) * 16), wb + (((5 + 2 * g8) ^ swzw(w8)) * 16)};
-  constexpr int FRB = WIN ? 4096 : 2048;  // bytes between fragments
-  // read t of the stage at byte offset so; hs: the stage's half of its K step (window mode only)
-  auto rd_one = [&](u32x4 (&fa)[2 * NBM], u32x4 (&fb)[2 * NBN], uint32_t so, int t, int hs) __attribute__((always_inline)) {
-    const uint32_t al = WIN ? fwa[2 * hs] : fa8l, ah = WIN ? fwa[2 * hs + 1] : fa8h;
-    const uint32_t bl = WIN ? fwb[2 * hs] : fb8l, bh = WIN ? fwb[2 * hs + 1] : fb8h;
-#define HILO_RD_CASE(C)                                                                                     \
-  case C:                                                                                                   \
-    if constexpr (C < 2 * NBN)                                                                              \
-      HILO_DS_READ16(fb[C % (2 * NBN)], ((C & 1) ? bh : bl) + so, ((C % (2 * NBN)) >> 1) * FRB);            \
-    else if constexpr (C < 2 * NBN + 2 * NBM)                                                               \
-      HILO_DS_READ16(fa[(C - 2 * NBN) % (2 * NBM)], ((C & 1) ? ah : al) + so, (((C - 2 * NBN) % (2 * NBM)) >> 1) * FRB); \
-    break;
-    switch (t) {
-      HILO_RD_CASE(0) HILO_RD_CASE(1) HILO_RD_CASE(2) HILO_RD_CASE(3) HILO_RD_CASE(4) HILO_RD_CASE(5)
-      HILO_RD_CASE(6) HILO_RD_CASE(7) HILO_RD_CASE(8) HILO_RD_CASE(9) HILO_RD_CASE(10) HILO_RD_CASE(11)
-      HILO_RD_CASE(12) HILO_RD_CASE(13) HILO_RD_CASE(14) HILO_RD_CASE(15)
-      default: break;
-    }
-#undef HILO_RD_CASE
-  };
-
-  // ---- epilogue operands of the current item: this wave's BN/2 columns (and FP8 rows) into its
-  // LDS area, by DMA (4 bytes per lane), indices clamped into the tile
-  uint8_t *epi = lds + (WIN ? G::WS * SBW : S * SB) + wid * kEpiWave;
-  TileRows etr{0, 0, 0, 1};
-  int en0 = 0;
-  auto epi_load = [&]() __attribute__((always_inline)) {
-    const int c0 = en0 + (wid & 1) * (BN / 2);
-    const uint16_t *bias = reinterpret_cast<const uint16_t *>(etr.sigma ? p.bias[1] : p.bias[0]);
-    g2lds4(bias + min(c0 + 2 * lane, p.N - 2), epi + kEpiBias);
-    if constexpr (F8) {
-      const float *ws = etr.sigma ? p.w_scale[1] : p.w_scale[0];
-      g2lds4(ws + min(c0 + lane, p.N - 1), epi + kEpiCol);
-      g2lds4(ws + min(c0 + 64 + lane, p.N - 1), epi + kEpiCol + 256);
-    }
-    if constexpr (EPI == EPI_RESID) {
-      const float *gate = p.mod + (size_t(etr.s * 2 + etr.sigma) * 6 + p.gate_idx) * p.D;
-      g2lds4(gate + min(c0 + lane, p.N - 1), epi + kEpiGate);
-      g2lds4(gate + min(c0 + 64 + lane, p.N - 1), epi + kEpiGate + 256);
-    }
-    if constexpr (F8) {
-      const int r0 = (wid >> 1) * (BM / 2);
-      g2lds4(p.a_scale + etr.row0 + min(r0 + lane, etr.nrows - 1), epi + kEpiRow);
-      g2lds4(p.a_scale + etr.row0 + min(r0 + 64 + lane, etr.nrows - 1), epi + kEpiRow + 256);
-    }
-  };
-
-  f32x16 acc[NBM][NBN];
-  u32x4 xa[2 * NBM], xb[2 * NBN], ya[2 * NBM], yb[2 * NBN];
-
-  // one stage (ring slot gs % S) on fragments (fa, fb); reads stage gs + 1 into (na, nb); the first
-  // stage of a tile (first = true_type) starts the accumulators from zero and, for a tile finished
-  // here, fetches the epilogue operands after its loads.  Before block NBN: barrier; after each of
-  // blocks NBN .. NBN + LQ - 1: one load of the stage three ahead and two fragment reads of the next.
-  auto stage = [&](auto first, auto odd, u32x4 (&fa)[2 * NBM], u32x4 (&fb)[2 * NBN], u32x4 (&na)[2 * NBM],
-                   u32x4 (&nb)[2 * NBN], int gs, bool with_epi) __attribute__((always_inline)) {
-    constexpr bool ODD = decltype(odd)::value;  // second stage of its K step
-    int lslot_w;
-    uint32_t so;
-    if constexpr (WIN) {
-      // window slot of this K step; loads go two K steps ahead, reads to the next stage
-      const int w3 = (gs >> 1) % G::WS;
-      lslot_w = w3 == 0 ? G::WS - 1 : w3 - 1;
-      so = uint32_t((ODD ? (w3 == G::WS - 1 ? 0 : w3 + 1) : w3) * SBW);
-    } else {
-      lslot_w = (gs + S - 1) & (S - 1);
-      so = uint32_t(((gs + 1) & (S - 1)) * SB);
-    }
-#pragma unroll
-    for (int bi = 0; bi < NBM; ++bi) {
-      // outstanding reads allowed: this stage's A halves of blocks bi+1.., the next stage's so far
-      wait_lgkm_rt(2 * (NBM - 1 - bi) + 2 * min(max(NBN * bi - NBN, 0), LQ));
-#pragma unroll
-      for (int bj = 0; bj < NBN; ++bj) {
-        const int qq = NBN * bi + bj;
-        if (qq == NBN) {
-          // window mode: the second stage of K step w waits for K step w + 1 (only the loads of w + 2
-          // issued by the first stage may be outstanding); the first stage reads the second half of
-          // its own K step, which is complete already.  Either barrier also frees the slot the stage
-          // loads into: every wave has finished the K step before.
-          if constexpr (!WIN) asm volatile("s_waitcnt vmcnt(%0)\n s_barrier" ::"n"((S - 3) * LQ) : "memory");
-          else if constexpr (ODD) asm volatile("s_waitcnt vmcnt(%0)\n s_barrier" ::"n"(LQ) : "memory");
-          else asm volatile("s_barrier" ::: "memory");
-        }
-        if constexpr (F8) {
-          if constexpr (decltype(first)::value)
-            HILO_MFMA8_AGPR0(acc[bi][bj], cat8(fb[2 * bj], fb[2 * bj + 1]), cat8(fa[2 * bi], fa[2 * bi + 1]));
-          else
-            HILO_MFMA8_AGPR(acc[bi][bj], cat8(fb[2 * bj], fb[2 * bj + 1]), cat8(fa[2 * bi], fa[2 * bi + 1]));
-        } else {
-          if constexpr (decltype(first)::value) HILO_MFMA16_AGPR0(acc[bi][bj], fb[2 * bj], fa[2 * bi]);
-          else HILO_MFMA16_AGPR(acc[bi][bj], fb[2 * bj], fa[2 * bi]);
-          HILO_MFMA16_AGPR(acc[bi][bj], fb[2 * bj + 1], fa[2 * bi + 1]);
-        }
-        if (qq >= NBN && qq < NBN + LQ) {
-          if constexpr (WIN) {
-            // the epilogue DMA goes ahead of the stage's loads, so the next stage's vmcnt covers it
-            if constexpr (decltype(first)::value) {
-              if (qq == NBN && with_epi) epi_load();
-            }
-            ld_win(lslot_w, ODD ? 1 : 0, qq - NBN);
-          } else {
-            ld_one(lslot_w, qq - NBN);
-          }
-          rd_one(na, nb, so, 2 * (qq - NBN), ODD ? 0 : 1);
-          rd_one(na, nb, so, 2 * (qq - NBN) + 1, ODD ? 0 : 1);
-        }
-        if constexpr (decltype(first)::value && !WIN) {
-          if (qq == NBN + LQ - 1 && with_epi) epi_load();
-        }
-      }
-    }
-    if constexpr (!WIN || ODD) ++lk;
-  };
-
-  SkCursor cc{pid, rg.beg};
-  SkItem cur = uni(sk_next_item(cc, q, rg, pid, p.part, T::kPartFloats));
-  if (!cur.valid) return;
-  ld_advance();  // the same first item
-  if constexpr (WIN) {
-    // the first two K steps, then wait for the first
-#pragma unroll 1
-    for (int wv = 0; wv < G::WS - 1; ++wv) {
-      if (lk == lke) ld_advance();
-#pragma unroll
-      for (int j = 0; j < NLA; ++j) ld_win(wv, 0, j);
-#pragma unroll
-      for (int j = 0; j < NLB; ++j) ld_win(wv, 1, j);
-      ++lk;
-    }
-    asm volatile("s_waitcnt vmcnt(%0)\n s_barrier" ::"n"(NLA + NLB) : "memory");
-  } else {
-#pragma unroll 1
-    for (int st = 0; st < S - 1; ++st) {
-      if (lk == lke) ld_advance();
-#pragma unroll
-      for (int j = 0; j < LQ; ++j) ld_one(st, j);
-      ++lk;
-    }
-    asm volatile("s_waitcnt vmcnt(%0)\n s_barrier" ::"n"((S - 2) * LQ) : "memory");
-  }
-#pragma unroll
-  for (int t = 0; t < NR; ++t) rd_one(xa, xb, 0, t, 0);
-
-  // the loader moves to its next item between stages, outside the MFMA schedule
-  auto ld_check = [&]() __attribute__((always_inline)) {
-    if (lk == lke) ld_advance();
-  };
-  int gs = 0;
-  while (true) {
-    const bool whole = cur.slot == nullptr;
-    if (whole) {
-      int rt, tn;
-      tile_coords(q, cur.t, rt, tn);
-      en0 = uni(tn) * BN;
-      etr = uni(decode_row_tile(p, BM, uni(rt)));
-    }
-    ld_check();
-    stage(std::true_type{}, std::false_type{}, xa, xb, ya, yb, gs, whole);
-    ld_check();
-    stage(std::false_type{}, std::true_type{}, ya, yb, xa, xb, gs + 1, false);
-    gs += 2;
-#pragma unroll 1
-    for (int kt = cur.kb + 1; kt < cur.ke; ++kt) {
-      ld_check();
-      stage(std::false_type{}, std::false_type{}, xa, xb, ya, yb, gs, false);
-      ld_check();
-      stage(std::false_type{}, std::true_type{}, ya, yb, xa, xb, gs + 1, false);
-      gs += 2;
-    }
-    // The last MFMAs' results must land before the accumulators are read (the empty asm ties each
-    // accumulator to this point, so no read is scheduled above it), and the reads of the next
-    // stage's fragments must be complete before the compiler may move those registers.
-    asm volatile("s_waitcnt lgkmcnt(0)\n s_nop 7\n s_nop 7\n s_nop 7\n s_nop 7" ::: "memory");
-#pragma unroll
-    for (int i = 0; i < NBM; ++i)
-#pragma unroll
-      for (int j = 0; j < NBN; ++j) asm volatile("" : "+a"(acc[i][j]));
-    if (whole) {
-      // the epilogue-operand DMA of the first stage is complete once two later stages have passed
-      // their barriers (each waits for all but the last stage's loads); a one-step item waits here.
-      // In window mode the item's second stage waited for it already.
-      if (!WIN && cur.ke - cur.kb < 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      if constexpr (F8 && EPI == EPI_BIAS && BN == 256) {
-        if (p.qk8 != nullptr && en0 < 2 * p.D) big_epilogue_qk8<BM, BN>(p, etr, en0, wid, lane, epi, acc);
-        else big_epilogue<BM, BN, EPI, F8>(p, etr, en0, wid, lane, epi, acc);
-      } else {
-        big_epilogue<BM, BN, EPI, F8>(p, etr, en0, wid, lane, epi, acc);
-      }
-    } else {
-      // the partial tile in the 16 x 16 fragment layout k_gemm_fix reads (2 NBM x 2 NBN fragments per
-      // wave): row 32 bi + l % 32 is fragment row 2 bi + (l % 32) / 16; columns 32 bj + 16 (l / 32)
-      // + 4 b .. + 3 are lane l % 16 + 16 b of fragment column 2 bj + l / 32
-      constexpr int TFM = 2 * NBM, TFN = 2 * NBN;
-      float *base = cur.slot + (size_t(wid) * TFM * TFN * 64 + ((lane & 31) >> 4) * TFN * 64 + (lane >> 5) * 64 + (lane & 15)) * 4;
-#pragma unroll
-      for (int bi = 0; bi < NBM; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < NBN; ++bj) {
-          f32x16 blk = acc[bi][bj];
-          asm volatile("" : "+v"(blk));
-#pragma unroll
-          for (int b = 0; b < 4; ++b)
-            *reinterpret_cast<f32x4 *>(base + ((2 * bi * TFN + 2 * bj) * 64 + 16 * b) * 4) =
-                f32x4{blk[4 * b], blk[4 * b + 1], blk[4 * b + 2], blk[4 * b + 3]};
-          asm volatile("" ::: "memory");
-        }
-    }
-    cur = uni(sk_next_item(cc, q, rg, pid, p.part, T::kPartFloats));
-    if (!cur.valid) break;
-  }
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-}
-
-// ------------------------------------------------------------------ bf16 tiles on eight waves
+// ----------------------------------------------------------- bf16 and FP8 tiles on eight waves
 //
 // One persistent workgroup of 8 waves per CU (2 x 4: wave tile BM/2 x BN/4 as 16 x 16 MFMA blocks, two
 // waves per SIMD).  A K step is a window of 64 values, 128-byte rows of A and W; LDS holds SLOTS windows
@@ -1042,40 +444,165 @@ __global__ __launch_bounds__(256) void k_gemm_big(GemmProblem p) {
 // 192, one wave per SIMD: every memory instruction held its only MFMA stream).  Two 4-wave groups in
 // ping-pong (one in its MFMAs, the other reading) ran 1370 and 1347 us; 32 x 32 MFMAs in this schedule
 // 1367; s_setprio around the MFMAs cost 1%.
+//
+// FP8: a window holds 128 values, and an FP8 MFMA takes the same cycles per operand byte as a bf16 one, so
+// the loads, reads and MFMA time per window are those of bf16.  256 x 256 tiles: v_mfma_f32_32x32x64_f8f6f4
+// per half (16 x 16 x 128 fragments of 32 bytes a lane would not fit twice), on 4 x 2 waves so that a wave
+// holds whole heads.  192 x 192 tiles: v_mfma_f32_16x16x128_f8f6f4 per window (the wave's 96 x 48 is not
+// whole 32 x 32 blocks).  64 x 64 step with the FP8 block 606 -> 586 us against one wave per SIMD, MLP half
+// on 7680 rows 697 -> 690.
 namespace g8 {
-constexpr int kEpi = 512;  // per wave, behind the windows: 64 columns of bias (bf16), then of the gate (float32)
-template <int BM, int BN>
+// A BM x BN tile of bf16 or FP8 operands on 8 waves: WM x WN waves, MB x NB blocks of 16 x 16 each (B32: of
+// 32 x 32).
+template <int BM, int BN, bool F8 = false>
 struct Geo {
-  static constexpr int MB = BM / 32, NB = BN / 64;  // 16 x 16 blocks per wave
+  static constexpr bool B32 = F8 && BN == 256;
+  static constexpr int WN = B32 ? 2 : 4, WM = 8 / WN;
+  static constexpr int MB = BM / WM / (B32 ? 32 : 16), NB = BN / WN / (B32 ? 32 : 16);
   static constexpr int LA = BM / 64, LB = BN / 64;  // load instructions per wave and window
   static constexpr int WB = (BM + BN) * 128;        // bytes of a window
+  static constexpr int KW = F8 ? 128 : 64;          // values of K in a window
+  // per wave, behind the windows: its columns of bias (bf16), of the gate (float32) and, for FP8, of the
+  // weight scales and its rows of activation scales (float32)
+  static constexpr int kGate = 256, kCol = 512, kRow = 1024, kEpi = F8 ? 1536 : 512;
   static constexpr int SLOTS = 3 * WB + 8 * kEpi <= 160 * 1024 ? 3 : 2;
   static constexpr int LDS = SLOTS * WB + 8 * kEpi;
 };
-HILO_DEV int swz(int r) { return (r >> 1) & 7; }
+// Chunk swizzle of window rows; B32 reads W rows in the order perm_w, whose 16-lane groups (rows 0-3, 16-19,
+// 4-7, 20-23, ...) need bit 4 in it to fall on 16 bank groups.
+template <bool B32>
+HILO_DEV int swz(int r) {
+  if constexpr (B32) return ((r >> 1) & 3) ^ ((((r >> 3) ^ (r >> 4)) & 1) << 2);
+  else return (r >> 1) & 7;
+}
+// W row read by fragment lane r of a 32 x 32 block.  The MFMA's output row i (the W side) lands in
+// accumulator register 4 (i / 8) + i % 4 of the lanes of half (i / 4) % 2; reading W row perm_w(i) there
+// gives lane half g the columns 16 g .. 16 g + 15 in register order.
+HILO_DEV int perm_w(int r) { return ((r & 4) ? 16 : 0) + 4 * (r >> 3) + (r & 3); }
 template <int V>
 struct Int {
   static constexpr int value = V;
 };
 template <int N>
 HILO_DEV void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+HILO_DEV i32x8 cat8(u32x4 lo, u32x4 hi) {
+  return __builtin_bit_cast(i32x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
 }  // namespace g8
 
-template <int OFF>
-HILO_DEV void ds_read16(bf16x8 &d, uint32_t addr) {
+template <int OFF, typename V>
+HILO_DEV void ds_read16(V &d, uint32_t addr) {
+  static_assert(sizeof(V) == 16);
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF) : "memory");
 }
 
+// FP8 tiles of 32 x 32 blocks (256 x 256, the wave's 64 x 128): lane l of block (bi, bj) holds row 32 bi +
+// l % 32 and columns 32 bj + 16 (l / 32) .. + 15 in register order.  The 16 values acc * (row scale * weight
+// scale) + bias of a block, operands from the wave's LDS area.
+template <typename G>
+HILO_DEV void values32(const uint8_t *epi, int lane, int bj, float sa, const f32x16 &blk, float (&v)[16]) {
+  const int cl = 16 * (lane >> 5) + 32 * bj;
+  u32x4 bu[2];
+  f32x4 cv[4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) bu[h] = *reinterpret_cast<const u32x4 *>(epi + 2 * cl + 16 * h);
+#pragma unroll
+  for (int h = 0; h < 4; ++h) cv[h] = *reinterpret_cast<const f32x4 *>(epi + G::kCol + 4 * cl + 16 * h);
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const uint32_t w = bu[e >> 3][(e >> 1) & 3];
+    const float bias = __uint_as_float((e & 1) ? (w & 0xffff0000u) : (w << 16));
+    v[e] = blk[e] * (sa * cv[e >> 2][e & 3]) + bias;
+  }
+}
+
+template <typename G>
+HILO_DEV void epilogue32(const GemmProblem &p, const TileRows &tr, int n0, int wm, int lane, const uint8_t *epi,
+                         f32x16 (&acc)[G::MB][G::NB]) {
+#pragma unroll
+  for (int bi = 0; bi < G::MB; ++bi) {
+    const int rl = (wm * G::MB + bi) * 32 + (lane & 31);
+    const float sa = *reinterpret_cast<const float *>(epi + G::kRow + 4 * (32 * bi + (lane & 31)));
+#pragma unroll
+    for (int bj = 0; bj < G::NB; ++bj) {
+      const int n = n0 + 32 * bj + 16 * (lane >> 5);
+      if (rl < tr.nrows && n < p.N) {  // N % 16 == 0: a lane's 16 columns are all inside or all out
+        float v[16];
+        values32<G>(epi, lane, bj, sa, acc[bi][bj], v);
+        uint4 *op = reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(p.out) + size_t(tr.row0 + rl) * p.ldo + n);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          op[h] = make_uint4(pack_bf16x2(v[8 * h + 0], v[8 * h + 1]), pack_bf16x2(v[8 * h + 2], v[8 * h + 3]),
+                             pack_bf16x2(v[8 * h + 4], v[8 * h + 5]), pack_bf16x2(v[8 * h + 6], v[8 * h + 7]));
+      }
+      asm volatile("" ::: "memory");  // the next block's operands stay below these stores
+    }
+  }
+}
+
+// FP8 q and k for the attention's score product, of a tile whose columns lie below 2 D.  The wave's 128
+// columns hold whole heads (128 / head_dim of them); per (row, head): the amax of the values over the head
+// -- this lane's 16 columns of each block and those of lane l ^ 32, which holds the block's other 16 -- the
+// power-of-two scale 2^k, the E4M3 codes of the values times 2^-k (16 bytes per lane and block) and one
+// E8M0 byte 127 + k.  The values are formed twice (amax, then codes) instead of held.
+template <typename G>
+HILO_DEV void epilogue32_qk8(const GemmProblem &p, const TileRows &tr, int n0, int wm, int lane, const uint8_t *epi,
+                             f32x16 (&acc)[G::MB][G::NB]) {
+  const int hd = p.head_dim, bph = hd / 32;  // blocks per head
+#pragma unroll
+  for (int bi = 0; bi < G::MB; ++bi) {
+    const float sa = *reinterpret_cast<const float *>(epi + G::kRow + 4 * (32 * bi + (lane & 31)));
+    float am0 = 0.f, am1 = 0.f;
+#pragma unroll
+    for (int bj = 0; bj < G::NB; ++bj) {
+      float v[16];
+      values32<G>(epi, lane, bj, sa, acc[bi][bj], v);
+      float m = 0.f;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) m = fmaxf(m, fabsf(v[e]));
+      if (bj / bph == 0) am0 = fmaxf(am0, m);
+      else am1 = fmaxf(am1, m);
+    }
+    am0 = fmaxf(am0, __shfl_xor(am0, 32, 64));
+    am1 = fmaxf(am1, __shfl_xor(am1, 32, 64));
+    const int k0 = pow2_exponent(am0), k1 = pow2_exponent(am1);
+    const float i0 = pow2_inverse(k0), i1 = pow2_inverse(k1);
+    const int rl = (wm * G::MB + bi) * 32 + (lane & 31);
+    if (rl < tr.nrows) {
+      uint8_t *row = p.qk8 + size_t(tr.row0 + rl) * p.ldq8;
+#pragma unroll
+      for (int bj = 0; bj < G::NB; ++bj) {
+        float v[16];
+        values32<G>(epi, lane, bj, sa, acc[bi][bj], v);
+        const float s = bj / bph == 0 ? i0 : i1;
+        uint4 c;
+        c.x = fp8x4(v[0] * s, v[1] * s, v[2] * s, v[3] * s);
+        c.y = fp8x4(v[4] * s, v[5] * s, v[6] * s, v[7] * s);
+        c.z = fp8x4(v[8] * s, v[9] * s, v[10] * s, v[11] * s);
+        c.w = fp8x4(v[12] * s, v[13] * s, v[14] * s, v[15] * s);
+        *reinterpret_cast<uint4 *>(row + n0 + 16 * (lane >> 5) + 32 * bj) = c;
+      }
+      if (lane < 32) {
+        row[2 * p.D + n0 / hd] = uint8_t(127 + k0);
+        if (bph * 2 == G::NB) row[2 * p.D + n0 / hd + 1] = uint8_t(127 + k1);
+      }
+    }
+    asm volatile("" ::: "memory");
+  }
+}
+
 // All work items of this workgroup under plan q on BM x BN tiles.
-template <int BM, int BN, int EPI>
+template <int BM, int BN, int EPI, bool F8 = false>
 HILO_DEV void gemm8_run(const GemmProblem &p, const SkPlan &q, int pid, uint8_t *lds) {
   using namespace g8;
-  using G = Geo<BM, BN>;
-  using T = SkTile<BM, BN, 2, 4, true>;
+  using G = Geo<BM, BN, F8>;
+  constexpr bool B32 = G::B32;
+  using T = SkTile<BM, BN, G::WM, G::WN, !B32>;
   constexpr int MB = G::MB, NB = G::NB, LA = G::LA, LB = G::LB, WB = G::WB, S = G::SLOTS;
+  constexpr int WM = G::WM, WN = G::WN, ESZ = F8 ? 1 : 2;  // ESZ: operand bytes per element
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lr = lane & 15, lg = lane >> 4, wm = wid >> 2, wn = wid & 3;
+  const int lr = lane & 15, lg = lane >> 4, wm = wid / WN, wn = wid % WN;
   const SkRange rg = sk_range(q, pid);
 
   // ---- loader: its own cursor over the items, S windows ahead of the MFMAs; wave wid loads rows
@@ -1099,15 +626,15 @@ HILO_DEV void gemm8_run(const GemmProblem &p, const SkPlan &q, int pid, uint8_t 
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
       const int r = wid * (BM / 8) + 8 * i + (lane >> 3);
-      oa[i] = uint32_t(min(r, tr.nrows - 1)) * uint32_t(p.lda) * 2 + uint32_t((lane & 7) ^ swz(r)) * 16;
+      oa[i] = uint32_t(min(r, tr.nrows - 1)) * uint32_t(p.lda) * ESZ + uint32_t((lane & 7) ^ swz<B32>(r)) * 16;
     }
 #pragma unroll
     for (int i = 0; i < LB; ++i) {
       const int r = wid * (BN / 8) + 8 * i + (lane >> 3);
-      ob[i] = uint32_t(min(r, p.N - 1 - n0)) * uint32_t(p.K) * 2 + uint32_t((lane & 7) ^ swz(r)) * 16;
+      ob[i] = uint32_t(min(r, p.N - 1 - n0)) * uint32_t(p.K) * ESZ + uint32_t((lane & 7) ^ swz<B32>(r)) * 16;
     }
-    la = reinterpret_cast<const char *>(p.A) + (size_t(tr.row0) * p.lda + size_t(x.kb) * 64) * 2;
-    lb = reinterpret_cast<const char *>(tr.sigma ? p.W[1] : p.W[0]) + (size_t(n0) * p.K + size_t(x.kb) * 64) * 2;
+    la = reinterpret_cast<const char *>(p.A) + (size_t(tr.row0) * p.lda + size_t(x.kb) * G::KW) * ESZ;
+    lb = reinterpret_cast<const char *>(tr.sigma ? p.W[1] : p.W[0]) + (size_t(n0) * p.K + size_t(x.kb) * G::KW) * ESZ;
     lk = x.kb;
     lke = x.ke;
   };
@@ -1126,64 +653,148 @@ HILO_DEV void gemm8_run(const GemmProblem &p, const SkPlan &q, int pid, uint8_t 
     lslot = lslot == S - 1 ? 0 : lslot + 1;
   };
 
-  // ---- fragments: lane (lr, lg) holds chunk 4 h + lg of row lr of a 16-row block.  W rows go in the
-  // order that gives the lane's accumulators 4 NB consecutive columns: MFMA output row 4 g + e of block
-  // j is column 4 NB g + 4 j + e of the wave
+  // ---- fragments, in chunks of 16 bytes.  bf16: lane (lr, lg) holds chunk 4 h + lg of row lr of a 16-row
+  // block in half h.  FP8, 16 x 16 blocks: both of these at once, for one 128-deep MFMA.  FP8, 32 x 32
+  // blocks: chunks 4 h + g and 4 h + 2 + g (g = lane / 32) of row lane % 32 for one 64-deep MFMA of half h.
+  // W rows of 16 x 16 blocks go in the order that gives the lane's accumulators 4 NB consecutive columns:
+  // MFMA output row 4 g + e of block j is column 4 NB g + 4 j + e of the wave
+  constexpr int NC = F8 ? 2 : 1;                       // chunks of a fragment
+  constexpr int NR = (MB + NB) * NC;                   // reads of a set: W first, then A
+  constexpr int NA = B32 ? 4 : 2;                      // chunk addresses of a lane
+  constexpr int RB = B32 ? 4096 : 2048;                // bytes between blocks
+  using Acc = std::conditional_t<B32, f32x16, f32x4>;
+  using Frag = std::conditional_t<F8, u32x4, bf16x8>;
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
-  uint32_t fa[2], fb[NB][2];
+  uint32_t fa[NA], fb[B32 ? 1 : NB][NA];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    fa[h] = lds0 + (wm * (BM / 2) + lr) * 128 + (((4 * h + lg) ^ swz(lr)) * 16);
+  for (int h = 0; h < NA; ++h) {
+    if constexpr (B32) {
+      const int r = lane & 31, w = perm_w(r), c = 2 * h + (lane >> 5);
+      fa[h] = lds0 + (wm * (BM / WM) + r) * 128 + ((c ^ swz<B32>(r)) * 16);
+      fb[0][h] = lds0 + (BM + wn * (BN / WN) + w) * 128 + ((c ^ swz<B32>(w)) * 16);
+    } else {
+      fa[h] = lds0 + (wm * (BM / WM) + lr) * 128 + (((4 * h + lg) ^ swz<B32>(lr)) * 16);
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int r = wn * (BN / 4) + (lr >> 2) * 4 * NB + 4 * j + (lr & 3);
-      fb[j][h] = lds0 + (BM + r) * 128 + (((4 * h + lg) ^ swz(r)) * 16);
+      for (int j = 0; j < NB; ++j) {
+        const int r = wn * (BN / WN) + (lr >> 2) * 4 * NB + 4 * j + (lr & 3);
+        fb[j][h] = lds0 + (BM + r) * 128 + (((4 * h + lg) ^ swz<B32>(r)) * 16);
+      }
     }
   }
-  f32x4 acc[MB][NB];
-  bf16x8 a[2][MB], b[2][NB];
+  Acc acc[MB][NB];
+  // Two sets: the halves of a window, or (FP8, 16 x 16) two windows.  The latter has no registers for two
+  // whole sets: rows 0 .. MB - 3 of A keep one fragment each, re-read once the row's MFMAs are issued
+  Frag a[2][MB][NC], b[2][NB][NC];
+  constexpr bool INP = F8 && !B32;
+  auto set_a = [](int h, int i) constexpr { return INP && i < MB - 2 ? 0 : h; };
   uint32_t so = 0;  // byte offset of the window being read
-  // read x of the fragments of half h: W first, then A
+  // read x of set h
   auto rd = [&](auto hh, auto xx) __attribute__((always_inline)) {
-    constexpr int h = decltype(hh)::value, x = decltype(xx)::value;
-    if constexpr (x < NB) ds_read16<0>(b[h][x], fb[x][h] + so);
-    else if constexpr (x < NB + MB) ds_read16<(x - NB) * 2048>(a[h][x - NB], fa[h] + so);
+    constexpr int h = decltype(hh)::value, x = decltype(xx)::value / NC, c = decltype(xx)::value % NC;
+    constexpr int ad = B32 ? 2 * h + c : F8 ? c : h;
+    if constexpr (x < NB) {
+      if constexpr (B32) ds_read16<(x < NB ? x : 0) * RB>(b[h][x][c], fb[0][ad] + so);
+      else ds_read16<0>(b[h][x][c], fb[x][ad] + so);
+    } else if constexpr (x < NB + MB) {
+      ds_read16<(x - NB) * RB>(a[set_a(h, x - NB)][x - NB][c], fa[ad] + so);
+    }
   };
   auto rd_wait = [&](auto hh) __attribute__((always_inline)) {
     constexpr int h = decltype(hh)::value;
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    // lgkmcnt(0), in the form the compiler's own wait tracking sees
+    __builtin_amdgcn_s_waitcnt(0xc07f);
 #pragma unroll
-    for (int i = 0; i < MB; ++i) asm volatile("" : "+v"(a[h][i]));
+    for (int c = 0; c < NC; ++c) {
 #pragma unroll
-    for (int j = 0; j < NB; ++j) asm volatile("" : "+v"(b[h][j]));
+      for (int i = 0; i < MB; ++i) asm volatile("" : "+v"(a[set_a(h, i)][i][c]));
+#pragma unroll
+      for (int j = 0; j < NB; ++j) asm volatile("" : "+v"(b[h][j][c]));
+    }
     __builtin_amdgcn_sched_barrier(0);
   };
-  // the MFMAs of half h; after each row of blocks a share of the reads of the other half, and (ld) the
-  // loads of a window into the slot just freed
-  auto half = [&](auto hh, bool ld) __attribute__((always_inline)) {
+  auto rd_all = [&](auto hh) __attribute__((always_inline)) {
+    auto r6 = [&](auto x) __attribute__((always_inline)) {
+      constexpr int x0 = decltype(x)::value;
+      if constexpr (x0 < NR) {
+        rd(hh, Int<x0>{}); rd(hh, Int<x0 + 1>{}); rd(hh, Int<x0 + 2>{});
+        rd(hh, Int<x0 + 3>{}); rd(hh, Int<x0 + 4>{}); rd(hh, Int<x0 + 5>{});
+      }
+    };
+    static_assert(NR <= 18, "reads of a set");
+    r6(Int<0>{}); r6(Int<6>{}); r6(Int<12>{});
+    rd_wait(hh);
+  };
+  // the MFMAs of set h in MB (B32: MB NB) groups; after each group a share of the reads of the other set,
+  // and (ld) the loads of a window into the slot just freed
+  auto half = [&](auto hh, auto ldd) __attribute__((always_inline)) {
     constexpr int h = decltype(hh)::value;
-    constexpr int RPB = (MB + NB + MB - 2) / (MB - 1);  // reads per row of blocks, none after the last
+    constexpr int GR = B32 ? MB * NB : MB;
+    constexpr int RPB = B32 || INP ? 2 : (NR + MB - 2) / (MB - 1);  // reads per group, none after the last
+    static_assert(RPB == 2, "reads per group of MFMAs");
     auto row = [&](auto ii) __attribute__((always_inline)) {
       constexpr int i = decltype(ii)::value;
-      if constexpr (i < MB) {
+      if constexpr (i < GR) {
+        if constexpr (B32) {
+          acc[i / NB][i % NB] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+              cat8(b[h][i % NB][0], b[h][i % NB][1]), cat8(a[h][i / NB][0], a[h][i / NB][1]), acc[i / NB][i % NB], 0, 0,
+              0, 0, 0, 0);
+        } else {
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[h][j], a[h][i], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < NB; ++j) {
+            if constexpr (F8)
+              acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+                  cat8(b[h][j][0], b[h][j][1]), cat8(a[set_a(h, i)][i][0], a[set_a(h, i)][i][1]), acc[i][j], 0, 0, 0, 0, 0,
+                  0);
+            else
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[h][j][0], a[h][i][0], acc[i][j], 0, 0, 0);
+          }
+        }
         __builtin_amdgcn_sched_barrier(0);
-        rd(Int<1 - h>{}, Int<i * RPB>{});
-        static_assert(RPB == 2, "reads per row of blocks");
-        rd(Int<1 - h>{}, Int<i * RPB + 1>{});
-        if (h == 1 && i == 0) ld_a();
-        if (h == 1 && i == MB / 2) ld_b();
+        if constexpr (INP) {
+          // after row i: A fragment i; W 0 and 1 after row 0, 2 after row 1, A MB - 2 and MB - 1 after 2 and 3
+          static_assert(MB == 6 && NB == 3, "read order of the FP8 tile");
+          if constexpr (i < 2) {
+            rd(Int<1 - h>{}, Int<4 * i>{});
+            rd(Int<1 - h>{}, Int<4 * i + 1>{});
+          }
+          if constexpr (i == 0) {
+            rd(Int<1 - h>{}, Int<2>{});
+            rd(Int<1 - h>{}, Int<3>{});
+          }
+          if constexpr (i < MB - 2) {
+            rd(Int<1 - h>{}, Int<2 * (NB + i)>{});
+            rd(Int<1 - h>{}, Int<2 * (NB + i) + 1>{});
+          }
+          if constexpr (i == 2 || i == 3) {
+            rd(Int<1 - h>{}, Int<2 * (NB + i + 2)>{});
+            rd(Int<1 - h>{}, Int<2 * (NB + i + 2) + 1>{});
+          }
+        } else {
+          rd(Int<1 - h>{}, Int<i * RPB>{});
+          rd(Int<1 - h>{}, Int<i * RPB + 1>{});
+        }
+        if constexpr (decltype(ldd)::value) {
+          if constexpr (i == 0) ld_a();
+          if constexpr (i == GR / 2) ld_b();
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
     };
     row(Int<0>{}); row(Int<1>{}); row(Int<2>{}); row(Int<3>{});
     row(Int<4>{}); row(Int<5>{}); row(Int<6>{}); row(Int<7>{});
   };
+  // this wave has read the window; all but the last window issued have landed (the epilogue's DMA, issued
+  // behind that one, only makes this wait stricter); on to the next
+  auto next_window = [&]() __attribute__((always_inline)) {
+    wait_vm<(S - 2) * (LA + LB)>();
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    so = so == (S - 1) * WB ? 0 : so + WB;
+    if (lk == lke) ld_advance();
+  };
 
-  // ---- epilogue operands of the current item: the wave's columns of bias and gate, by DMA
-  uint8_t *epi = lds + S * WB + wid * kEpi;
+  // ---- epilogue operands of the current item: the wave's columns of bias, gate and scales, by DMA
+  uint8_t *epi = lds + S * WB + wid * G::kEpi;
   SkCursor cc{pid, rg.beg};
   SkItem cur = uni(sk_next_item(cc, q, rg, pid, p.part, T::kPartFloats));
   if (!cur.valid) return;
@@ -1203,45 +814,84 @@ HILO_DEV void gemm8_run(const GemmProblem &p, const SkPlan &q, int pid, uint8_t 
     if (whole) {
       int rt, tn;
       tile_coords(q, cur.t, rt, tn);
-      en0 = uni(tn) * BN + wn * (BN / 4);
+      en0 = uni(tn) * BN + wn * (BN / WN);
       etr = uni(decode_row_tile(p, BM, uni(rt)));
       const uint16_t *bias = reinterpret_cast<const uint16_t *>(etr.sigma ? p.bias[1] : p.bias[0]);
-      g2lds4(bias + min(en0 + 2 * (lane & 31), p.N - 2), epi);
+      g2lds4(bias + min(en0 + 2 * lane, p.N - 2), epi);
       if constexpr (EPI == EPI_RESID)
-        g2lds4(p.mod + (size_t(etr.s * 2 + etr.sigma) * 6 + p.gate_idx) * p.D + min(en0 + lane, p.N - 1), epi + 256);
+        g2lds4(p.mod + (size_t(etr.s * 2 + etr.sigma) * 6 + p.gate_idx) * p.D + min(en0 + lane, p.N - 1), epi + G::kGate);
+      if constexpr (F8) {
+        const float *ws = etr.sigma ? p.w_scale[1] : p.w_scale[0];
+        const int r0 = wm * (BM / WM);
+        g2lds4(ws + min(en0 + lane, p.N - 1), epi + G::kCol);
+        if constexpr (BN / WN > 64) g2lds4(ws + min(en0 + 64 + lane, p.N - 1), epi + G::kCol + 256);
+        g2lds4(p.a_scale + etr.row0 + min(r0 + lane, etr.nrows - 1), epi + G::kRow);
+        if constexpr (BM / WM > 64) g2lds4(p.a_scale + etr.row0 + min(r0 + 64 + lane, etr.nrows - 1), epi + G::kRow + 256);
+      }
     }
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
-      for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < NB; ++j) acc[i][j] = Acc(0.f);
     // the first window's first fragments (again, after an epilogue: it needs their registers)
-    auto r0 = [&](auto x) __attribute__((always_inline)) { rd(Int<0>{}, x); };
-    r0(Int<0>{}); r0(Int<1>{}); r0(Int<2>{}); r0(Int<3>{}); r0(Int<4>{}); r0(Int<5>{});
-    r0(Int<6>{}); r0(Int<7>{}); r0(Int<8>{}); r0(Int<9>{}); r0(Int<10>{}); r0(Int<11>{});
-    rd_wait(Int<0>{});
+    rd_all(Int<0>{});
+    if constexpr (INP) {
+      int kt = cur.kb;
 #pragma unroll 1
-    for (int kt = cur.kb; kt < cur.ke; ++kt) {
-      half(Int<0>{}, false);
-      rd_wait(Int<1>{});
-      // window kt is read by this wave; all but the last window issued have landed (the epilogue's DMA,
-      // issued behind that one, only makes this wait stricter)
-      wait_vm<(S - 2) * (LA + LB)>();
-      asm volatile("s_barrier" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
-      so = so == (S - 1) * WB ? 0 : so + WB;
-      if (lk == lke) ld_advance();
-      half(Int<1>{}, true);
-      rd_wait(Int<0>{});
+      for (; kt + 1 < cur.ke; kt += 2) {
+        next_window();
+        half(Int<0>{}, std::true_type{});
+        rd_wait(Int<1>{});
+        next_window();
+        half(Int<1>{}, std::true_type{});
+        rd_wait(Int<0>{});
+      }
+      if (kt < cur.ke) {
+        next_window();
+        half(Int<0>{}, std::true_type{});
+        rd_wait(Int<1>{});
+      }
+    } else {
+#pragma unroll 1
+      for (int kt = cur.kb; kt < cur.ke; ++kt) {
+        half(Int<0>{}, std::false_type{});
+        rd_wait(Int<1>{});
+        next_window();
+        half(Int<1>{}, std::true_type{});
+        rd_wait(Int<0>{});
+      }
     }
     if (whole) {
       // a one-step item's epilogue operands may still be in flight
       if (cur.ke - cur.kb < 2) wait_vm<0>();
+    }
+    if constexpr (B32) {
+      static_assert(EPI != EPI_RESID && EPI != EPI_GELU, "epilogues of 32 x 32 blocks");
+      if (whole) {
+        if (p.qk8 != nullptr && en0 < 2 * p.D) epilogue32_qk8<G>(p, etr, en0, wm, lane, epi, acc);
+        else epilogue32<G>(p, etr, en0, wm, lane, epi, acc);
+      } else {
+        // the fixup's 16 x 16 order: row 32 bi + l % 32 is fragment row 2 bi + (l % 32) / 16; columns 32 bj
+        // + 16 (l / 32) + 4 c .. + 3 are lane l % 16 + 16 c of fragment column 2 bj + l / 32
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+              *reinterpret_cast<f32x4 *>(cur.slot + T::part_index(wid, 2 * i + ((lane & 31) >> 4), 2 * j + (lane >> 5),
+                                                                  lr + 16 * c)) =
+                  f32x4{acc[i][j][4 * c], acc[i][j][4 * c + 1], acc[i][j][4 * c + 2], acc[i][j][4 * c + 3]};
+      }
+    } else if (whole) {
       uint2 bu[NB];
+      f32x4 wsc[F8 ? NB : 1];
       f32x4 gv[NB];
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
         bu[j] = *reinterpret_cast<const uint2 *>(epi + 2 * (4 * NB * lg + 4 * j));
-        if constexpr (EPI == EPI_RESID) gv[j] = *reinterpret_cast<const f32x4 *>(epi + 256 + 4 * (4 * NB * lg + 4 * j));
+        if constexpr (EPI == EPI_RESID) gv[j] = *reinterpret_cast<const f32x4 *>(epi + G::kGate + 4 * (4 * NB * lg + 4 * j));
+        if constexpr (F8) wsc[j] = *reinterpret_cast<const f32x4 *>(epi + G::kCol + 4 * (4 * NB * lg + 4 * j));
       }
       const int nc = en0 + 4 * NB * lg;
       // the residual update keeps the z pieces of three batches of two row blocks in flight, in the
@@ -1253,7 +903,7 @@ HILO_DEV void gemm8_run(const GemmProblem &p, const SkPlan &q, int pid, uint8_t 
       auto ld_z = [&](int set, int i0) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < ZR; ++i) {
-          const int rl = wm * (BM / 2) + 16 * (i0 + i) + lr;
+          const int rl = wm * (BM / WM) + 16 * (i0 + i) + lr;
           const float *zr = p.z + size_t(etr.row0 + min(rl, etr.nrows - 1)) * p.ldz;
 #pragma unroll
           for (int j = 0; j < NB; ++j) z[set][i][j] = *reinterpret_cast<const f32x4 *>(zr + min(nc + 4 * j, p.N - 4));
@@ -1268,14 +918,27 @@ HILO_DEV void gemm8_run(const GemmProblem &p, const SkPlan &q, int pid, uint8_t 
       for (int i0 = 0; i0 < MB; i0 += ZR) {
 #pragma unroll
         for (int ii = 0; ii < ZR; ++ii) {
-          const int i = i0 + ii, rl = wm * (BM / 2) + 16 * i + lr;
+          const int i = i0 + ii, rl = wm * (BM / WM) + 16 * i + lr;
+          // taken here whether used or not: a load still pending at the K loop would put a vmcnt(0) into it
+          if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+            for (int j = 0; j < NB; ++j) asm volatile("" : "+v"(z[i0 / ZR % ZS][ii][j]));
+          }
           if (rl < etr.nrows) {
             const size_t m = size_t(etr.row0 + rl);
             uint2 o[NB];
+            float sa;
+            if constexpr (F8) sa = *reinterpret_cast<const float *>(epi + G::kRow + 4 * (16 * i + lr));
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
-              float v[4] = {acc[i][j][0] + __uint_as_float(bu[j].x << 16), acc[i][j][1] + __uint_as_float(bu[j].x & 0xffff0000u),
-                            acc[i][j][2] + __uint_as_float(bu[j].y << 16), acc[i][j][3] + __uint_as_float(bu[j].y & 0xffff0000u)};
+              float v[4];
+              const float bv[4] = {__uint_as_float(bu[j].x << 16), __uint_as_float(bu[j].x & 0xffff0000u),
+                                   __uint_as_float(bu[j].y << 16), __uint_as_float(bu[j].y & 0xffff0000u)};
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                if constexpr (F8) v[e] = acc[i][j][e] * (sa * wsc[j][e]) + bv[e];
+                else v[e] = acc[i][j][e] + bv[e];
+              }
               if constexpr (EPI == EPI_RESID) {
                 f32x4 zn = z[i0 / ZR % ZS][ii][j];
 #pragma unroll
@@ -1447,6 +1110,13 @@ HILO_DEV Tile choose_tile(const GemmProblem &p, int &rows) {
   return t;
 }
 
+template <int BM, int BN, int EPI, int ROLE>
+__global__ __launch_bounds__(512, 2) void k_gemm8_fp8(GemmProblem p) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[g8::Geo<BM, BN, true>::LDS];
+  const int pid = xcd_remap(blockIdx.x, kGemmWorkgroups);
+  gemm8_run<BM, BN, EPI, true>(p, sk_plan(p, row_tiles_total(p, BM), BN, 128), pid, lds);
+}
+
 template <int EPI, int ROLE>
 __global__ __launch_bounds__(512, 2) void k_gemm8(GemmProblem p) {
   constexpr int L0 = g8::Geo<192, 192>::LDS, L1 = g8::Geo<256, 256>::LDS;
@@ -1554,8 +1224,9 @@ HILO_DEV void gemm_fix(const GemmProblem &p, const SkPlan &q) {
 }
 
 template <int BM, int BN, int EPI, int ROLE>
-__global__ __launch_bounds__(kFixThreads) void k_gemm_fix(GemmProblem p) {
-  gemm_fix<BM, BN, 2, 2, false, EPI, true>(p, sk_plan(p, row_tiles_total(p, BM), BN, 128));
+__global__ __launch_bounds__(kFixThreads) void k_gemm8_fp8_fix(GemmProblem p) {
+  using G = g8::Geo<BM, BN, true>;
+  gemm_fix<BM, BN, G::WM, G::WN, !G::B32, EPI, true>(p, sk_plan(p, row_tiles_total(p, BM), BN, 128));
 }
 
 template <int EPI, int ROLE>
@@ -1651,21 +1322,20 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmProblem p) {
 
 // ------------------------------------------------------------------------------- dispatch
 
-// BM x BN tiles: one persistent workgroup per CU.
-template <int BM, int BN, int ROLE, bool F8 = false>
-static hipError_t run_big(const GemmProblem &p, hipStream_t st) {
+// FP8: one persistent workgroup per CU, BM x BN tiles.
+template <int BM, int BN, int ROLE>
+static hipError_t run_fp8(const GemmProblem &p, hipStream_t st) {
   static_assert(size_t(BM) * BN * 3 * kGemmWorkgroups * sizeof(float) <= kSkPartBytes, "partial area too small");
   constexpr int P = kGemmWorkgroups;
-  hipLaunchKernelGGL((k_gemm_big<BM, BN, role_epilogue(ROLE), ROLE, F8>), dim3(P), dim3(256), 0, st, p);
+  hipLaunchKernelGGL((k_gemm8_fp8<BM, BN, role_epilogue(ROLE), ROLE>), dim3(P), dim3(512), 0, st, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const bool long_k = p.K / (F8 ? 128 : 64) > kNoSplitSteps;
   const long long tiles_max = (long long)p.B * ((p.max_img_rows + BM - 1) / BM + (p.L + BM - 1) / BM) *
                               ((p.N + BN - 1) / BN);
-  if (tiles_max < P && !long_k) return hipSuccess;
+  if (tiles_max < P && p.K / 128 <= kNoSplitSteps) return hipSuccess;
   // P workgroups stride over the fixup's items: few enough that a launch with nothing to finish
   // (the device's row counts led to whole tiles) costs little
-  hipLaunchKernelGGL((k_gemm_fix<BM, BN, role_epilogue(ROLE), ROLE>), dim3(P), dim3(kFixThreads), 0, st, p);
+  hipLaunchKernelGGL((k_gemm8_fp8_fix<BM, BN, role_epilogue(ROLE), ROLE>), dim3(P), dim3(kFixThreads), 0, st, p);
   return hipGetLastError();
 }
 
@@ -1700,12 +1370,6 @@ hipError_t launch_gemm(bool bf16, int role, const GemmProblem &p, hipStream_t st
       default: return run_f32<EPI_RESID>(p, st);
     }
   }
-  // Every projection on 192 x 192 tiles, whose K steps run through the LDS as whole 128-byte
-  // lines.  At 2766 rows (the 64 x 64 workload): QKV 720 tiles in three whole waves, MLP up 960 in
-  // four, the attention output and MLP down (N = 3072) 240 tiles in one wave with no K split.  256 x
-  // 256 tiles (half-line stages) cost slightly less per output but quantise these row counts worse:
-  // QKV took 178 us as two launches (256 x 256, then 256 x 192 for the columns one wave could not
-  // hold) against 161, MLP up 230 us as two waves plus a stream-K tail against 218.
   switch (role) {
     case GEMM_QKV: return run_bf16<GEMM_QKV>(p, st);
     case GEMM_O: return run_bf16<GEMM_O>(p, st);
@@ -1717,10 +1381,10 @@ hipError_t launch_gemm(bool bf16, int role, const GemmProblem &p, hipStream_t st
 hipError_t launch_gemm_fp8(int role, const GemmProblem &p, hipStream_t st) {
   switch (role) {
     // the FP8 QKV projection always writes FP8 q / k: 256-column tiles (whole heads per wave)
-    case GEMM_QKV: return p.qk8 ? run_big<256, 256, GEMM_QKV, true>(p, st) : hipErrorInvalidValue;
-    case GEMM_O: return run_big<192, 192, GEMM_O, true>(p, st);
-    case GEMM_FC1: return run_big<192, 192, GEMM_FC1, true>(p, st);
-    default: return run_big<192, 192, GEMM_FC2, true>(p, st);
+    case GEMM_QKV: return p.qk8 ? run_fp8<256, 256, GEMM_QKV>(p, st) : hipErrorInvalidValue;
+    case GEMM_O: return run_fp8<192, 192, GEMM_O>(p, st);
+    case GEMM_FC1: return run_fp8<192, 192, GEMM_FC1>(p, st);
+    default: return run_fp8<192, 192, GEMM_FC2>(p, st);
   }
 }
 

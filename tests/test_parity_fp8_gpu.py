@@ -351,6 +351,22 @@ def test_fp8_gemm_schedules(shp):
     assert_close(to_np(db.y_img), ref["y_img"], "fp8", "y_img")
 
 
+# the FP8 tiles' K loop runs windows of 128 values in pairs on 192 x 192 tiles: one, two and three windows (MLP
+# down with mlp_dim 128, 256, 384), row tails around a tile's edge, and both head dims of the QKV epilogue
+@pytest.mark.parametrize("mlp,hd,grid,text", [(128, 128, 14, 1), (256, 64, 28, 65), (384, 128, 16, 191)])
+def test_fp8_window_counts(mlp, hd, grid, text):
+    print(f"[parity-fp8] windows mlp={mlp} hd={hd} grid={grid} text={text}", flush=True)
+    shp = inputs.BlockShape(1, 1, grid, grid, text, 256, 256 // hd, hd, mlp, "bf16")
+    wl = inputs.make_workload("fp8windows", shape=shp, seed=11, keep_frac=0.9)
+    db = DeviceBlock(wl)
+    db.prepare_fp8()
+    db.score()
+    db.select(hilo.TOPK)
+    db.compress()
+    torch.cuda.synchronize()
+    fp8_block_checked(db, wl)
+
+
 @pytest.mark.parametrize("name", ["small128", "small64"])
 def test_fp8_fused_compress_norm(name):
     """The FP8 block with its attention half's first row norm in the compress pass
