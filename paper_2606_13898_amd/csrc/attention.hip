@@ -3,7 +3,7 @@
 //
 // bf16 path (gfx950 MFMA v_mfma_f32_16x16x32_bf16, fp32 online softmax in base 2):
 //   workgroup = NW waves x QW query rows of one (sample, head) (head dim 128: 8 x 32, one
-//   workgroup per CU; 64: 4 x 32, two per CU); K/V stream through LDS in tiles of 64 keys, double
+//   workgroup per CU; 64: 4 x 32, three per CU); K/V stream through LDS in tiles of 64 keys, double
 //   buffered.  Each wave computes S^T = K Q^T so that every lane owns one query
 //   row's scores (4 keys per 16-key subtile): the running max stays lane-local, and the
 //   probabilities are already in the register layout of the second MFMA operand for
@@ -119,7 +119,7 @@ HILO_DEV void g2lds16(const void *g, void *lds_wave_base) {
 // Stream-K schedule of the attention core.  A unit is (sample, head, query tile of QW*NW rows);
 // it takes nkv(s) = ceil(n_s / 64) key steps.  Units are ordered sample-major, then head, then
 // query tile (the query tiles of one head share its keys in L2), and the P persistent workgroups
-// take equal contiguous ranges of the (unit, key step) space.  A unit fully inside one range is
+// (attn_parts of them) take equal contiguous ranges of the (unit, key step) space.  A unit fully inside one range is
 // finished there; a cut unit leaves per-range partial results (unnormalised O, running max m and
 // sum l per query row) that k_attn_fix merges in range order: M = max m_i,
 // O = sum exp2(m_i - M) O_i / sum exp2(m_i - M) l_i.
@@ -150,6 +150,21 @@ HILO_DEV AttnUnit attn_unit(const int *cu, int B, int heads, int BQ, long long i
     base += span;
   }
   return AttnUnit{0, 0, 0, 1, 0};
+}
+
+// Workgroups that share I key steps (both the core and the merge derive it).  A range costs its steps, a cut
+// unit one partial per range to write and merge in turn, so a small problem goes to ranges of a few steps
+// rather than to every CU: at least 2, and up to 8 (head dim 64) or 4 (128) from 512 or 256 steps on.
+// Measured against one range per workgroup of the grid (core and merge): head dim 64, 24 heads x 600 tokens
+// 25.6 -> 20.3 us (4 steps 21.4, 16 steps 26.5), 4 x 1100 29.0 -> 18.7, 2 x (320 + 361) 17.0 -> 12.4 (4 steps
+// 14.7); head dim 128, 24 x 600 37.4 -> 32.7 (8 steps 36.9), 8 x 704 38.5 -> 32.0, 2 x (320 + 361) 25.9 -> 23.2.
+template <int HD>
+HILO_DEV int attn_parts(long long I) {
+  constexpr uint32_t most = HD == 128 ? 4 : 8;
+  if (I >= (long long)most * gridDim.x) return gridDim.x;
+  const uint32_t i = uint32_t(I), s = min(max(i / 64, 2u), most);
+  // uniform, as the loops over its ranges must stay (the division runs on the vector ALU)
+  return __builtin_amdgcn_readfirstlane(min((i + s - 1) / s, gridDim.x));
 }
 
 struct AttnArgs {
@@ -204,8 +219,10 @@ HILO_DEV void attn_store_out(const AttnArgs &a, const AttnUnit &u, int wid, int 
   }
 }
 
+// Head dim 64 has registers for three workgroups of 4 waves per CU (at most 168 each), which hide more of
+// each other's softmax than two: 24 heads x 7680 tokens 471 -> 436 us, 2766 tokens level.
 template <int HD, int QW, int NW, bool F8S>
-__global__ __launch_bounds__(NW * 64, 8 / NW) void k_attn_bf16(AttnArgs a) {
+__global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 3) void k_attn_bf16(AttnArgs a) {
   using S = AttnShape<HD, QW, NW>;
   constexpr int BKV = 64;
   constexpr int QS = S::QS;         // query subtiles per wave
@@ -225,9 +242,10 @@ __global__ __launch_bounds__(NW * 64, 8 / NW) void k_attn_bf16(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) uint8_t sK8[2][F8S ? BKV * HD : 16];
   __shared__ __attribute__((aligned(256))) uint32_t sKs[2][F8S ? BKV : 4];
 
-  const int P = gridDim.x;
-  const int pid = xcd_remap(blockIdx.x, P);
   const long long I = attn_iterations(a.cu, a.B, a.heads, BQ);
+  const int P = attn_parts<HD>(I);
+  if (int(blockIdx.x) >= P) return;
+  const int pid = xcd_remap(blockIdx.x, P);
   const long long beg = I * pid / P, end = I * (pid + 1) / P;
   if (beg >= end) return;
   const long long head_start = attn_unit(a.cu, a.B, a.heads, BQ, beg).start;
@@ -554,9 +572,10 @@ template <int HD, int QW, int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_fix(AttnArgs a) {
   using S = AttnShape<HD, QW, NW>;
   constexpr int QS = S::QS, DS = S::DS, BQ = S::BQ;
-  const int P = gridDim.x;
-  const int pid = blockIdx.x;
   const long long I = attn_iterations(a.cu, a.B, a.heads, BQ);
+  const int P = attn_parts<HD>(I);
+  const int pid = blockIdx.x;
+  if (pid >= P) return;
   const long long beg = I * pid / P, end = I * (pid + 1) / P;
   if (beg >= end) return;
   const AttnUnit u = attn_unit(a.cu, a.B, a.heads, BQ, end - 1);
@@ -798,8 +817,7 @@ static hipError_t run_attn_bf16(const void *qkv, const int *cu, void *out, float
   static_assert(S::kSlotFloats <= 2 * kAttnSlotFloats, "partial slot too large for the workspace");
   AttnArgs a{reinterpret_cast<const uint16_t *>(qkv), cu, reinterpret_cast<uint16_t *>(out), part, B,
              heads, kLog2e / sqrtf(float(HD)), qk8, ldq8};
-  // 4 waves: two workgroups per CU; 8 waves: one (two waves per SIMD either way)
-  const int P = attn_workgroups(NW == 8 ? 1 : 2, S::kSlotFloats);
+  const int P = attn_workgroups(NW == 8 ? 1 : 3, S::kSlotFloats);
   if (qk8) hipLaunchKernelGGL((k_attn_bf16<HD, QW, NW, true>), dim3(P), dim3(NW * 64), 0, st, a);
   else hipLaunchKernelGGL((k_attn_bf16<HD, QW, NW, false>), dim3(P), dim3(NW * 64), 0, st, a);
   hipError_t e = hipGetLastError();
@@ -825,7 +843,7 @@ static hipError_t run_attn_f32(const void *qkv, const int *cu, void *out, int B,
 size_t attention_part_bytes(bool bf16, int hd) {
   if (!bf16) return 0;
   const size_t slot = hd == 128 ? AttnShape<128, 32, 8>::kSlotFloats : AttnShape<64, 32, 4>::kSlotFloats;
-  return size_t(2) * attn_workgroups(hd == 128 ? 1 : 2, slot) * slot * sizeof(float);
+  return size_t(2) * attn_workgroups(hd == 128 ? 1 : 3, slot) * slot * sizeof(float);
 }
 
 hipError_t launch_attention(bool bf16, const void *qkv, const int *cu, void *out, float *part, int B,

@@ -96,7 +96,8 @@ hipError_t launch_gemm(bool bf16, int role, const GemmProblem &p, hipStream_t st
 hipError_t launch_gemm_fp8(int role, const GemmProblem &p, hipStream_t st);
 
 // Stream-K partial results of the bf16 attention core (part of the caller's workspace): two
-// slots per workgroup, each the unnormalised output and running max / sum of one query tile.
+// slots per workgroup, each the unnormalised output and running max / sum of one query tile.  512 are
+// counted at 128 query rows of head dim 128; smaller slots leave room for more workgroups.
 constexpr int kAttnMaxWorkgroups = 512;
 constexpr size_t kAttnSlotFloats = size_t(4) * 2 * 8 * 64 * 4 + size_t(4) * 2 * 64 * 2;
 constexpr size_t kAttnPartBytes = size_t(kAttnMaxWorkgroups) * 2 * kAttnSlotFloats * sizeof(float);

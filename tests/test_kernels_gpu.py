@@ -29,6 +29,27 @@ def test_attention_core_f32(hd, lens, heads):
     assert_close(to_np(out), O.attention_core(qkv, cu, heads), "f32", "float32 attention core")
 
 
+# the bf16 core gives a problem of I key steps (units of 128 or 256 queries x tiles of 64 keys) to ranges of 2
+# to 4 or 8 steps: an empty one, a single step, odd counts around 2 steps a range, the growing range (128 to 512
+# steps), and the last size below one range per workgroup of the grid
+@pytest.mark.parametrize("hd,lens,heads", [(64, [0], 2), (64, [1], 2), (64, [65, 0, 129], 1), (64, [320, 361], 2),
+                                           (64, [1100], 4), (64, [600], 24), (128, [1], 2), (128, [193, 64], 3),
+                                           (128, [257, 320], 2), (128, [704], 8), (128, [600], 24)])
+def test_attention_core_bf16(hd, lens, heads):
+    print(f"[kernel] bf16 attention core hd={hd} heads={heads} lens={lens}", flush=True)
+    cu, D = _cu(lens), heads * hd
+    qkv = torch.from_numpy(np.random.default_rng(hd + sum(lens)).standard_normal((max(1, int(cu[-1])), 3 * D)))
+    qkv = qkv.to(torch.bfloat16)
+    shp = hilo.hilo_shape(len(lens), 1, 2, 2 * ((max(lens) + 7) // 4), 0, D, heads, hd, 4 * D, hilo.BF16)
+    out = torch.full((qkv.shape[0], D), 7.0, dtype=torch.bfloat16, device="cuda")
+    hilo.hilo_attention_core_noalloc(shp, qkv.cuda(), torch.from_numpy(cu).cuda(), out)
+    torch.cuda.synchronize()
+    if cu[-1] == 0:
+        assert (out == 7.0).all()
+        return
+    assert_close(to_np(out), O.attention_core(qkv.float().numpy(), cu, heads), "bf16", "bf16 attention core")
+
+
 def run_mlp(shape, lens, seed, rows=None):
     """hilo_mlp on packed rows of the given sample lengths -> (z after, oracle's z), for `rows` if given."""
     rng = np.random.default_rng(seed)
