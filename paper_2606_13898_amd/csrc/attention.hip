@@ -159,12 +159,12 @@ HILO_DEV AttnUnit attn_unit(const int *cu, int B, int heads, int BQ, long long i
 // 25.6 -> 20.3 us (4 steps 21.4, 16 steps 26.5), 4 x 1100 29.0 -> 18.7, 2 x (320 + 361) 17.0 -> 12.4 (4 steps
 // 14.7); head dim 128, 24 x 600 37.4 -> 32.7 (8 steps 36.9), 8 x 704 38.5 -> 32.0, 2 x (320 + 361) 25.9 -> 23.2.
 template <int HD>
-HILO_DEV int attn_parts(long long I) {
+HILO_DEV int attn_parts(long long I, uint32_t grid) {
   constexpr uint32_t most = HD == 128 ? 4 : 8;
-  if (I >= (long long)most * gridDim.x) return gridDim.x;
+  if (I >= (long long)most * grid) return grid;
   const uint32_t i = uint32_t(I), s = min(max(i / 64, 2u), most);
   // uniform, as the loops over its ranges must stay (the division runs on the vector ALU)
-  return __builtin_amdgcn_readfirstlane(min((i + s - 1) / s, gridDim.x));
+  return __builtin_amdgcn_readfirstlane(min((i + s - 1) / s, grid));
 }
 
 struct AttnArgs {
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 3) void k_attn_bf16(AttnArgs
   __shared__ __attribute__((aligned(256))) uint32_t sKs[2][F8S ? BKV : 4];
 
   const long long I = attn_iterations(a.cu, a.B, a.heads, BQ);
-  const int P = attn_parts<HD>(I);
+  const int P = attn_parts<HD>(I, gridDim.x);
   if (int(blockIdx.x) >= P) return;
   const int pid = xcd_remap(blockIdx.x, P);
   const long long beg = I * pid / P, end = I * (pid + 1) / P;
@@ -567,14 +567,17 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 3) void k_attn_bf16(AttnArgs
   }
 }
 
-// Merges every unit cut by range boundaries; run by the range holding the unit's first key step.
+// Merges every unit cut by range boundaries, under the number of the range holding the unit's first key step: a
+// workgroup of one wave for each wave of that range, so that a unit's partials (up to 142 KiB each) come in
+// through several CUs.  Core and merge against one workgroup of NW waves per range: head dim 128, 2 heads x
+// (320 + 361) tokens 22.3 -> 17.2 us, 8 x 704 32.0 -> 25.8, 24 x 600 32.8 -> 30.1, 24 x 2766 120 -> 118.
 template <int HD, int QW, int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_fix(AttnArgs a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_fix(AttnArgs a) {
   using S = AttnShape<HD, QW, NW>;
   constexpr int QS = S::QS, DS = S::DS, BQ = S::BQ;
   const long long I = attn_iterations(a.cu, a.B, a.heads, BQ);
-  const int P = attn_parts<HD>(I);
-  const int pid = blockIdx.x;
+  const int P = attn_parts<HD>(I, gridDim.x / NW);
+  const int pid = blockIdx.x / NW, wid = blockIdx.x % NW;
   if (pid >= P) return;
   const long long beg = I * pid / P, end = I * (pid + 1) / P;
   if (beg >= end) return;
@@ -582,7 +585,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const long long ue = u.start + u.nkv;
   if (end >= ue) return;      // the unit ends inside this range: not cut here
   if (beg > u.start) return;  // this range does not hold the unit's first step
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int lane = threadIdx.x;
 
   f32x4 o[QS][DS];
   float m[QS], l[QS];
@@ -822,7 +825,7 @@ static hipError_t run_attn_bf16(const void *qkv, const int *cu, void *out, float
   else hipLaunchKernelGGL((k_attn_bf16<HD, QW, NW, false>), dim3(P), dim3(NW * 64), 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_attn_fix<HD, QW, NW>), dim3(P), dim3(NW * 64), 0, st, a);
+  hipLaunchKernelGGL((k_attn_fix<HD, QW, NW>), dim3(P * NW), dim3(64), 0, st, a);
   return hipGetLastError();
 }
 
