@@ -126,7 +126,7 @@ HILO_DEV TileRows decode_row_tile(const GemmProblem &p, int BM, int r) {
 // remaining units (all of the same K length) are spread evenly over the P workgroups stream-K,
 // so no CU idles through a partial last wave.  A unit not finished in one place leaves an fp32
 // partial tile (data-parallel unit u: slot u; stream-K range of workgroup w: slots P + 2w for its
-// first unit and P + 2w + 1 for its second); k_gemm_fix adds the partials of each such tile in a
+// first unit and P + 2w + 1 for its second); gemm_fix adds the partials of each such tile in a
 // fixed order and runs the epilogue -- deterministic, and no workgroup ever waits for another.
 struct SkPlan {
   int R, TN, T, nk;  // row tiles, column tiles, tiles, K steps

@@ -1,6 +1,6 @@
 """The stream-K GEMM schedule's arithmetic, modelled on the host.
 
-The kernels (gemm.hip: sk_plan, sk_range, sk_owner, sk_next_item and k_gemm_fix's contributor
+The kernels (gemm.hip: sk_plan, sk_range, sk_owner, sk_next_item and gemm_fix's contributor
 walk) split T tiles of nk K steps over P workgroups: whole data-parallel units first, then a
 stream-K tail over the first Pk workgroups, whose range cuts leave fp32 partial tiles that the fixup
 adds.  This model restates those formulas and checks, for fixed and random (T, P, nk), that every

@@ -126,16 +126,15 @@ def load(out, cnt, tag):
 
 
 def gemm_role(base):
-    """Projection of a GEMM kernel from its template arguments: k_gemm_fix<BM, BN, WM, WN, EPI, ROLE,
-    F8>, k_gemm_big<BM, BN, EPI, ROLE, F8>."""
-    args = [a.strip() for a in base[base.index("<") + 1:base.rindex(">")].split(",")]
-    return ROLES[args[3] if base.startswith("hilo::k_gemm_big") else args[5]]
+    """Projection of a GEMM kernel from its last template argument: k_gemm8<EPI, ROLE>, k_gemm8_fp8<BM,
+    BN, EPI, ROLE> and their fixups."""
+    return ROLES[base[base.index("<") + 1:base.rindex(">")].split(",")[-1].strip()]
 
 
 def kind_of(name, state):
     """Bench kernel kind of a dispatch; rownorm launches alternate attention / MLP per step."""
     base = name.split("(")[0].replace("void ", "").strip()
-    if "k_gemm_fix<" in base or "k_gemm_big<" in base:
+    if "k_gemm8" in base:
         return gemm_role(base)
     if "k_attn" in base:
         return "attention_core"
@@ -157,7 +156,7 @@ def kind_of(name, state):
 
 def is_main(name):
     """A kernel that does a call's MFMA work (not a GEMM fixup or the attention merge)."""
-    return "k_gemm_fix" not in name and "k_attn_fix" not in name
+    return not ("k_gemm8" in name and "_fix<" in name) and "k_attn_fix" not in name
 
 
 def primary(name):
