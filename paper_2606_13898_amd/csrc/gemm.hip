@@ -415,6 +415,12 @@ HILO_DEV float *uni(float *ptr) {
   return reinterpret_cast<float *>((uint64_t(hi) << 32) | lo);
 }
 HILO_DEV SkItem uni(const SkItem &x) { return SkItem{uni(x.t), uni(x.kb), uni(x.ke), uni(x.slot), uni(int(x.valid)) != 0}; }
+// v, of which nothing derived is known before this point: what an epilogue or a tile switch forms from the
+// lane number is then formed there, not hoisted out of the item loop and kept in registers through the K loop.
+HILO_DEV int opaque(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
 HILO_DEV TileRows uni(const TileRows &x) { return TileRows{uni(x.s), uni(x.sigma), uni(x.row0), uni(x.nrows)}; }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -623,6 +629,7 @@ HILO_DEV void gemm8_run(const GemmProblem &p, const SkPlan &q, int pid, uint8_t 
     tile_coords(q, x.t, rt, tn);
     const TileRows tr = uni(decode_row_tile(p, BM, uni(rt)));
     const int n0 = uni(tn) * BN;
+    const int lane = opaque(threadIdx.x & 63);
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
       const int r = wid * (BM / 8) + 8 * i + (lane >> 3);
@@ -865,6 +872,7 @@ HILO_DEV void gemm8_run(const GemmProblem &p, const SkPlan &q, int pid, uint8_t 
       // a one-step item's epilogue operands may still be in flight
       if (cur.ke - cur.kb < 2) wait_vm<0>();
     }
+    const int lane = opaque(threadIdx.x & 63), lr = lane & 15, lg = lane >> 4;
     if constexpr (B32) {
       static_assert(EPI != EPI_RESID && EPI != EPI_GELU, "epilogues of 32 x 32 blocks");
       if (whole) {
@@ -894,19 +902,27 @@ HILO_DEV void gemm8_run(const GemmProblem &p, const SkPlan &q, int pid, uint8_t 
         if constexpr (F8) wsc[j] = *reinterpret_cast<const f32x4 *>(epi + G::kCol + 4 * (4 * NB * lg + 4 * j));
       }
       const int nc = en0 + 4 * NB * lg;
-      // the residual update keeps the z pieces of three batches of two row blocks in flight, in the
-      // registers the fragments leave free: stores count in vmcnt, so a load issued behind them waits
-      // for them too (a batch at a time cost one memory round trip each: 35 us on a 256 x 256 tile)
-      constexpr int ZR = EPI == EPI_RESID ? 2 : 1, ZS = 3;
+      // the residual update keeps the z pieces of ZS batches of two row blocks in flight: stores count in
+      // vmcnt, so a load issued behind them waits for them too.  Two batches of a 256 x 256 tile are 64
+      // registers beside its 128 accumulators, a third would not fit (64 registers went to scratch, whose
+      // accesses wait for each other and for the loads in flight); on 192 x 192 three are the whole tile.
+      // 25004 rows in 8 samples: output 541 -> 515 us, MLP down 1653 -> 1600 against the three that spilled.
+      constexpr int ZR = EPI == EPI_RESID ? 2 : 1, ZS = NB == 4 ? 2 : 3;
       static_assert(MB % ZR == 0, "row blocks per batch");
       f32x4 z[ZS][ZR][NB];
+      // z is addressed by 32-bit offsets from the tile's first row (at most 256 rows of 8192 values)
+      char *zt = reinterpret_cast<char *>(p.z + size_t(etr.row0) * p.ldz);
+      auto zoff = [&](int r, int j) __attribute__((always_inline)) {
+        // N % 64 == 0: a lane's 16 columns of a 256-wide tile are all inside or all out
+        const int n = NB == 4 ? min(nc, p.N - 16) + 4 * j : min(nc + 4 * j, p.N - 4);
+        return (uint32_t(r) * uint32_t(p.ldz) + uint32_t(n)) * 4;
+      };
       auto ld_z = [&](int set, int i0) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < ZR; ++i) {
           const int rl = wm * (BM / WM) + 16 * (i0 + i) + lr;
-          const float *zr = p.z + size_t(etr.row0 + min(rl, etr.nrows - 1)) * p.ldz;
 #pragma unroll
-          for (int j = 0; j < NB; ++j) z[set][i][j] = *reinterpret_cast<const f32x4 *>(zr + min(nc + 4 * j, p.N - 4));
+          for (int j = 0; j < NB; ++j) z[set][i][j] = *reinterpret_cast<const f32x4 *>(zt + zoff(min(rl, etr.nrows - 1), j));
         }
       };
       if constexpr (EPI == EPI_RESID) {
@@ -943,7 +959,7 @@ HILO_DEV void gemm8_run(const GemmProblem &p, const SkPlan &q, int pid, uint8_t 
                 f32x4 zn = z[i0 / ZR % ZS][ii][j];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) zn[e] += gv[j][e] * v[e];
-                if (nc + 4 * j < p.N) *reinterpret_cast<f32x4 *>(p.z + m * p.ldz + nc + 4 * j) = zn;
+                if (nc + 4 * j < p.N) *reinterpret_cast<f32x4 *>(zt + zoff(rl, j)) = zn;
               } else {
                 if constexpr (EPI == EPI_GELU) {
 #pragma unroll
@@ -1065,11 +1081,15 @@ HILO_DEV void gemm_small_run(const GemmProblem &p, int rows, int pid, uint8_t *l
 // The tile of a projection, chosen on the device (only it knows the row counts; the main kernel and the
 // fixup derive the same one): the shorter of two estimates in units of 10 ns, from measured rounds.  A
 // K step takes 1.46 us on a 256 x 256 tile and 0.91 on 192 x 192; a tile adds its prologue and epilogue,
-// 7 and 4 us, or 43 and 16 where it updates z (every workgroup reads and writes its tile's z at once, at
-// the copy rate).  A plan that cuts tiles spreads the K steps evenly and adds its partials and their
-// fixup, about 30 and 20 us; a turn of TILE_SMALL is described at gemm_small_run.  2766 rows of a 64 x 64 grid: 192 x 192 for all four projections (QKV 151 us
-// against 168, output 69 / 115, MLP up 196 / 198, MLP down 191 / 225); 25000 rows in 8 samples: 256 x 256
-// (QKV 1208 against 1256, MLP up 1535 / 1660, MLP down 1640 / 1675) but for the output (561 / 553).
+// 7 and 4 us, or 40 and 16 where it updates z (every workgroup reads and writes its tile's z at once, 26
+// and 14 us at the copy rate).  A plan that cuts tiles spreads the K steps evenly and adds its partials and
+// their fixup, about 30 and 20 us; a turn of TILE_SMALL is described at gemm_small_run.  2766 rows of a 64 x
+// 64 grid: 192 x 192 for all four projections (QKV 151 us against 168, output 70 / 108, MLP up 196 / 198,
+// MLP down 188 / 223); 25000 rows in 8 samples: 256 x 256 (QKV 1208 against 1256, MLP up 1535 / 1660, MLP
+// down 1600 / 1658) but for the output, which 256 x 256 would do in 515 against 533.  The cost of a tile that
+// updates z measured 33 to 45 us over D 1024 .. 4096 and 700 .. 25000 rows; at 34, which would give that
+// output to 256 x 256, D 1536 at 6300 rows (74 us against 65) and MLP down of D 3072 at 3100 rows (281
+// against 245) would go there too.
 template <int EPI>
 HILO_DEV uint32_t plan_cost(uint32_t T, uint32_t nk, uint32_t step, uint32_t tile, uint32_t tile_z, uint32_t cut) {
   constexpr uint32_t P = kGemmWorkgroups;
@@ -1095,7 +1115,7 @@ HILO_DEV Tile choose_tile(const GemmProblem &p, int &rows) {
   uint32_t best = plan_cost<EPI>(r192 * ((p.N + 191) / 192), nk, 91, 400, 1600, 2000);
   rows = r192;
   Tile t = TILE_192;
-  const uint32_t c256 = plan_cost<EPI>(r256 * ((p.N + 255) / 256), nk, 146, 700, 4300, 3000);
+  const uint32_t c256 = plan_cost<EPI>(r256 * ((p.N + 255) / 256), nk, 146, 700, 4000, 3000);
   if (c256 < best) {
     best = c256;
     rows = r256;
