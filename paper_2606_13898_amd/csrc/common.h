@@ -23,6 +23,13 @@ HILO_DEV int xcd_remap(int b, int n) {
   return x * q + (x < r ? x : r) + k;
 }
 
+// v, of which nothing derived is known before this point: what rarely executed code forms from the lane number
+// is then formed there, not hoisted out of the loop around it and kept in registers through that loop.
+HILO_DEV int opaque(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 HILO_DEV float bf2f(uint16_t b) { return __uint_as_float(uint32_t(b) << 16); }
 
 // float -> bf16 bits, round to nearest even (NaN stays NaN).

@@ -415,12 +415,6 @@ HILO_DEV float *uni(float *ptr) {
   return reinterpret_cast<float *>((uint64_t(hi) << 32) | lo);
 }
 HILO_DEV SkItem uni(const SkItem &x) { return SkItem{uni(x.t), uni(x.kb), uni(x.ke), uni(x.slot), uni(int(x.valid)) != 0}; }
-// v, of which nothing derived is known before this point: what an epilogue or a tile switch forms from the
-// lane number is then formed there, not hoisted out of the item loop and kept in registers through the K loop.
-HILO_DEV int opaque(int v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
 HILO_DEV TileRows uni(const TileRows &x) { return TileRows{uni(x.s), uni(x.sigma), uni(x.row0), uni(x.nrows)}; }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));

@@ -94,3 +94,33 @@ def test_mlp_bf16(dim, mlp, lens, text):
     rows = None if T < 2500 and dim < 512 else np.sort(np.random.default_rng(5).choice(T, 160, replace=False))
     got, want = run_mlp(shape, lens, 4, rows)
     assert_close(got, want, "bf16", "bf16 MLP")
+
+
+# one key of every 64-key tile outweighs the tile's others by 2^40, so a short problem's probabilities are 1 or
+# nothing in units of their tile's maximum and the output's only rounding in 16 bits is its own (half of 2^-7 relative);
+# the maxima rise, fall and fall by more than the reference may.  Ranges of 2, 4 and 8 tiles, whole and cut units,
+# and a last tile of one key.
+@pytest.mark.parametrize("hd,n,heads", [(64, 128, 2), (64, 256, 32), (64, 512, 64), (64, 449, 24), (128, 128, 2),
+                                        (128, 321, 12), (128, 256, 64)])
+def test_attention_core_bf16_short_precision(hd, n, heads):
+    print(f"[kernel] bf16 attention core precision hd={hd} heads={heads} n={n}", flush=True)
+    rng = np.random.default_rng(hd + n + heads)
+    D, tiles = heads * hd, (n + 63) // 64
+    qkv = np.zeros((n, 3, heads, hd), np.float32)
+    unit = np.sqrt(hd) * np.log(2.0)  # a score of one in base 2
+    qkv[:, 0, :, 0] = inputs.to_bf16_values(rng.uniform(0.75, 1.25, (n, heads)).astype(np.float32))
+    level = rng.choice([0.0, 1.3, -1.7, 2.9, -0.6, -30.0], (tiles, heads))
+    level[rng.integers(tiles, size=heads), np.arange(heads)] = 0.0
+    score = np.repeat(level, 64, axis=0)[:n] - 60.0
+    for t in range(tiles):
+        score[rng.integers(64 * t, min(n, 64 * t + 64), size=heads), np.arange(heads)] = level[t]
+    qkv[:, 1, :, 0] = inputs.to_bf16_values((score * unit).astype(np.float32))
+    qkv[:, 2] = inputs.to_bf16_values(rng.standard_normal((n, heads, hd)).astype(np.float32))
+    qkv, cu = qkv.reshape(n, 3 * D), _cu([n])
+    shp = hilo.hilo_shape(1, 1, 2, 2 * ((n + 3) // 4), 0, D, heads, hd, 4 * D, hilo.BF16)
+    out = torch.empty(n, D, dtype=torch.bfloat16, device="cuda")
+    hilo.hilo_attention_core_noalloc(shp, torch.from_numpy(qkv).to(torch.bfloat16).cuda(), torch.from_numpy(cu).cuda(), out)
+    torch.cuda.synchronize()
+    want = O.attention_core(qkv, cu, heads)
+    over = np.abs(to_np(out).astype(np.float64) - want) - (2.0 ** -8 * np.abs(want) + 1e-5 * np.abs(qkv[:, 2 * D:]).max())
+    assert over.max() <= 0, (over.max(), (over > 0).mean())
