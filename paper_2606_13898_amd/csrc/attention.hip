@@ -729,7 +729,7 @@ __global__ __launch_bounds__(NW * 64) void k_attn_f32(const float *__restrict__ 
   #pragma unroll
     for (int t = 0; t < KF; ++t) o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;  // l: this lane's own keys only, summed over the lane groups at the end
-    auto tile = [&](int t, const f32x4 (&kf)[KF], const f32x4 (&vf)[4][VF]) __attribute__((always_inline)) {
+    auto tile = [&](int t, const f32x4 (&kf)[KF], f32x4 (&vf)[4][VF]) __attribute__((always_inline)) {
       f32x4 sa[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};  // two independent chains
   #pragma unroll
       for (int c = 0; c < KF; ++c)
@@ -740,7 +740,12 @@ __global__ __launch_bounds__(NW * 64) void k_attn_f32(const float *__restrict__ 
       if (16 * t + 16 > n) {
   #pragma unroll
         for (int r = 0; r < 4; ++r)
-          if (16 * t + 4 * lg + r >= n) sc[r] = -INFINITY;
+          if (16 * t + 4 * lg + r >= n) {
+            sc[r] = -INFINITY;
+            // no key: the row re-read in its place may hold an infinity, which its probability 0 would make a NaN
+  #pragma unroll
+            for (int c = 0; c < VF; ++c) vf[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+          }
       }
       const float mt = xmax16_32(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])));
       if (__any(mt > m)) {

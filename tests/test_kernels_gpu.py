@@ -124,3 +124,20 @@ def test_attention_core_bf16_short_precision(hd, n, heads):
     want = O.attention_core(qkv, cu, heads)
     over = np.abs(to_np(out).astype(np.float64) - want) - (2.0 ** -8 * np.abs(want) + 1e-5 * np.abs(qkv[:, 2 * D:]).max())
     assert over.max() <= 0, (over.max(), (over > 0).mean())
+
+
+# an infinite value of the last key, with its 16-key tile and its wave's turn partly past the sequence: every
+# query's output is infinite in that dim and finite in the others
+@pytest.mark.parametrize("hd,n", [(64, 17), (64, 130), (128, 31)])
+def test_attention_core_f32_infinite_value(hd, n):
+    print(f"[kernel] float32 attention core, infinite value hd={hd} n={n}", flush=True)
+    qkv, cu = np.random.default_rng(n).standard_normal((n, 3 * hd)).astype(np.float32), _cu([n])
+    qkv[n - 1, 2 * hd + 5] = np.inf
+    want = O.attention_core(np.where(np.isinf(qkv), 0, qkv), cu, 1)
+    shp = hilo.hilo_shape(1, 1, 2, 2 * ((n + 3) // 4), 0, hd, 1, hd, 4 * hd, hilo.F32)
+    out = torch.empty(n, hd, device="cuda")
+    hilo.hilo_attention_core(shp, torch.from_numpy(qkv).cuda(), torch.from_numpy(cu).cuda(), out)
+    torch.cuda.synchronize()
+    got = to_np(out)
+    assert np.all(got[:, 5] == np.inf)
+    assert_close(np.delete(got, 5, 1), np.delete(want, 5, 1), "f32", "finite dims")
