@@ -750,15 +750,17 @@ __global__ __launch_bounds__(NW * 64) void k_attn_f32(const float *__restrict__ 
       const float mt = xmax16_32(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])));
       if (__any(mt > m)) {
         const float mnew = fmaxf(m, mt);
-        const float alpha = __builtin_amdgcn_exp2f(m - mnew);
+        const float alpha = __builtin_amdgcn_exp2f(m - (mnew == -INFINITY ? 0.f : mnew));
         l *= alpha;
   #pragma unroll
         for (int d = 0; d < KF; ++d) o[d] *= alpha;
         m = mnew;
       }
+      // a query whose scores so far are all -inf has no maximum to subtract: its probabilities are 0
+      const float ref = m == -INFINITY ? 0.f : m;
       f32x4 p;
   #pragma unroll
-      for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(sc[r] - m);
+      for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(sc[r] - ref);
       l += (p[0] + p[1]) + (p[2] + p[3]);
   #pragma unroll
       for (int j = 0; j < 4; ++j)

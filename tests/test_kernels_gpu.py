@@ -141,3 +141,22 @@ def test_attention_core_f32_infinite_value(hd, n):
     got = to_np(out)
     assert np.all(got[:, 5] == np.inf)
     assert_close(np.delete(got, 5, 1), np.delete(want, 5, 1), "f32", "finite dims")
+
+
+# scores of -inf that fill a wave's only tile (a lone last key) or several:
+# these keys count nothing and every output is finite
+@pytest.mark.parametrize("hd,n,keys", [(64, 17, [16]), (64, 300, list(range(16, 32))), (128, 145, [144]),
+                                       (128, 40, list(range(16, 40)))])
+def test_attention_core_f32_infinite_scores(hd, n, keys):
+    print(f"[kernel] float32 attention core, scores of -inf hd={hd} n={n}", flush=True)
+    qkv, cu = np.random.default_rng(n).standard_normal((n, 3 * hd)).astype(np.float32), _cu([n])
+    qkv[:, 7] = np.abs(qkv[:, 7]) + 0.1   # the queries' component that meets the keys' -inf
+    qkv[keys, hd + 7] = -np.inf
+    shp = hilo.hilo_shape(1, 1, 2, 2 * ((n + 3) // 4), 0, hd, 1, hd, 4 * hd, hilo.F32)
+    out = torch.empty(n, hd, device="cuda")
+    hilo.hilo_attention_core(shp, torch.from_numpy(qkv).cuda(), torch.from_numpy(cu).cuda(), out)
+    torch.cuda.synchronize()
+    q, k, v = (qkv[:, i * hd:(i + 1) * hd].astype(np.float64) for i in range(3))
+    score = q @ k.T / np.sqrt(hd)
+    p = np.exp(score - score.max(1, keepdims=True))
+    assert_close(to_np(out), p / p.sum(1, keepdims=True) @ v, "f32", "float32 attention core")
