@@ -86,8 +86,12 @@ struct GemmProblem {
 };
 
 // Partial-sum area of the GEMMs (part of the caller's workspace): one slot per data-parallel unit
-// of a split wave plus two per workgroup for its stream-K range, one fp32 256 x 256 tile per slot,
-// one workgroup per CU (256; no workgroup waits for another, so fewer CUs would do).
+// of a split wave plus two per workgroup for its stream-K range, one fp32 256 x 256 tile per slot.  The
+// workgroups are the CUs of a whole MI355X.  On a partition of one, with fewer, they run in turns (none waits
+// for another) on a plan made for 256: results are the same, each turn pays a prologue of about 3 us, and
+// problems of fewer than 256 tiles are cut finer than that device needs.  With the number an argument of the
+// launch (a power of two, divisions as shifts) the bf16 projections ran level, FP8 QKV 90.3 -> 91.5 us and MLP up
+// 115.3 -> 116.6 at 2766 rows.
 constexpr int kGemmWorkgroups = 256;
 constexpr size_t kSkPartBytes = size_t(kGemmWorkgroups) * 3 * 256 * 256 * sizeof(float);
 hipError_t launch_gemm(bool bf16, int role, const GemmProblem &p, hipStream_t st);
