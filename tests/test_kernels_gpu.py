@@ -6,6 +6,7 @@ import torch
 from oracle import hilo_oracle as O
 from paper_2606_13898_amd import hilo, inputs
 from parity_util import assert_close, to_np
+from schedule_model import MLP_SHAPES
 
 pytestmark = pytest.mark.gpu
 
@@ -79,14 +80,9 @@ def test_mlp_f32(dim, mlp, lens, text):
     assert_close(got, want, "f32", "float32 MLP")
 
 
-# the bf16 projections choose their tile from the row counts (tests/test_gemm_schedule.py models the
-# plans of the large ones).  Small tiles: K of one, three and five steps over four waves, row tails, more
-# tiles than workgroups; 192 x 192 tiles of one K step, N below a tile; 256 whole 256 x 256 tiles, then
-# 12 of 192 x 192 cut into 22 pieces and a stream-K tail; 1040 tiles of 256 x 256 in four whole waves
-# and a stream-K tail that cuts 16
-@pytest.mark.parametrize("dim,mlp,lens,text", [(64, 320, [193, 65], 31), (192, 960, [705, 64, 1], 0),
-                                               (64, 320, [1100, 901], 31), (512, 16384, [600], 40),
-                                               (2048, 13312, [5100], 0)])
+# the bf16 projections choose their tile and plan from the row counts: schedule_model.py says which each of
+# these shapes reaches, and test_gemm_schedule.py checks that it does
+@pytest.mark.parametrize("dim,mlp,lens,text", [shape for shape, _ in MLP_SHAPES])
 def test_mlp_bf16(dim, mlp, lens, text):
     print(f"[kernel] bf16 MLP dim={dim} mlp={mlp} lens={lens} text={text}", flush=True)
     shape = inputs.BlockShape(len(lens), 1, 2, 2 * ((max(lens) + 3) // 4), text, dim, dim // 64, 64, mlp, "bf16")

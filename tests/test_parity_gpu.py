@@ -11,6 +11,7 @@ from paper_2606_13898_amd.pipeline import DeviceBlock, DeviceStack
 
 from parity_util import (assert_close, assert_update_close, check_compressed, check_selection,
                          float_report, midpoint_tau, oracle_for, to_np)
+from schedule_model import BLOCK_SHAPES, SPLIT_K_SHAPES
 
 pytestmark = pytest.mark.gpu
 
@@ -243,18 +244,13 @@ def test_attention_core_ragged(hd, lens, heads):
     assert_close(to_np(out), want, "bf16", f"attention core hd={hd}")
 
 
-@pytest.mark.parametrize("shp", [
-    # down projection: ~6 tiles, K = 8192 (128 steps) -> tiles cut into K pieces plus a stream-K tail
-    inputs.BlockShape(3, 1, 16, 20, 40, 256, 2, 128, 8192, "bf16"),
-    # a single 192 x 192 down-projection tile (at most 144 rows, N = 192): every K piece is one
-    # step, the fixup sums 128 partial tiles
-    inputs.BlockShape(1, 1, 12, 12, 0, 192, 3, 64, 8192, "bf16"),
-], ids=["pieces_and_tail", "one_tile_128_pieces"])
-def test_mlp_split_k(shp):
+@pytest.mark.parametrize("name", list(SPLIT_K_SHAPES))
+def test_mlp_split_k(name):
     """MLP with a long down-projection K and few output tiles: the projection is split along K
     and finished by the fixup; every row of z is compared with the oracle."""
+    shp = SPLIT_K_SHAPES[name][0]
     print(f"[parity] split-K mlp shape={shp}", flush=True)
-    wl = inputs.make_workload("splitk", shape=shp, seed=11)
+    wl = inputs.make_workload("splitk", shape=shp, seed=11, keep_frac=1.0)
     db = DeviceBlock(wl)
     ref = oracle_for(wl)
     db.run(hilo.TOPK)
@@ -265,21 +261,12 @@ def test_mlp_split_k(shp):
     assert_close(to_np(db.y_img), ref["y_img"], "bf16", "y_img split-K")
 
 
-# On a 256-CU device these reach every schedule of the 192 x 192 GEMM tiling (tests/
-# test_gemm_schedule.py models the same plans); every block is kept fine so the row counts are fixed.
-@pytest.mark.parametrize("shp", [
-    # 12 + 2 row tiles x 19 column tiles = 266 MLP-up tiles of 16 K steps: one wave of whole tiles,
-    # then a 10-tile stream-K tail over 14 workgroups whose range boundaries cut tiles (fixup)
-    inputs.BlockShape(1, 1, 48, 48, 256, 1024, 8, 128, 3648, "bf16"),
-    # 22 + 2 row tiles x 16 = 384 MLP-up tiles: the last wave holds 128 >= 128 tiles, so two waves of
-    # whole tiles
-    inputs.BlockShape(1, 1, 64, 64, 256, 256, 2, 128, 3072, "bf16"),
-    # few tiles and K = 4608 (72 steps): QKV cut into 2 K pieces plus a stream-K tail, the attention
-    # output into 6, MLP up into 22 pieces of three or four steps
-    inputs.BlockShape(1, 1, 16, 16, 0, 4608, 36, 128, 1024, "bf16"),
-], ids=["sk_tail", "whole_waves", "k_pieces"])
-def test_gemm_schedules(shp):
-    print(f"[parity] 192-tile GEMM schedules shape={shp}", flush=True)
+# Whole blocks whose projections reach the schedules that schedule_model.py lists beside each shape (checked in
+# test_gemm_schedule.py); every block is kept fine so the row counts are fixed.
+@pytest.mark.parametrize("name", list(BLOCK_SHAPES))
+def test_gemm_schedules(name):
+    shp = BLOCK_SHAPES[name][0]
+    print(f"[parity] GEMM schedules shape={shp}", flush=True)
     wl = inputs.make_workload("splitk", shape=shp, seed=5, keep_frac=1.0)
     db = DeviceBlock(wl)
     ref = oracle_for(wl)
