@@ -260,8 +260,8 @@ HILO_DEV SkItem sk_next_item(SkCursor &c, const SkPlan &q, const SkRange &rg, in
 
 // Partial tiles of a BM x BN tile on WM x WN waves, in the 16 x 16 fragment order the fixup
 // reads, and the fixup's epilogue of one fragment row.
-// CONTIG: a lane's columns of all fragment columns are consecutive (the 8-wave kernel), instead of 4 of
-// every 16.
+// CONTIG: a lane's columns of all fragment columns are consecutive (16 x 16 blocks), instead of 4 of every 16
+// (the 32 x 32 blocks of the FP8 QKV projection).
 template <int BM, int BN, int WM, int WN, bool CONTIG = false>
 struct SkTile {
   static constexpr int NW = WM * WN;
@@ -279,8 +279,8 @@ struct SkTile {
   // The FP8 q / k codes of fragment row i0 of wave wid (the whole-tile form is epilogue32_qk8):
   // the wave's BN / WN columns hold whole heads; a row's columns of one head are spread over the 4
   // lanes l % 16 + 16 m, each holding 4 columns of every 16.
-  HILO_DEV static void epilogue_rows_qk8(const GemmProblem &p, const TileRows &tr, int n0, int wid, int i0,
-                                         int lane, const f32x4 (&acc)[1][TN]) {
+  HILO_DEV static void epilogue_row_qk8(const GemmProblem &p, const TileRows &tr, int n0, int wid, int i0,
+                                        int lane, const f32x4 (&acc)[TN]) {
     const int rl = (wid / WN) * (BM / WM) + i0 * 16 + (lane & 15);
     const int wc0 = n0 + (wid % WN) * (BN / WN);
     const int cbase = wc0 + 4 * (lane >> 4);
@@ -297,10 +297,10 @@ struct SkTile {
       const float4 wsc = *reinterpret_cast<const float4 *>(ws + nc);
       const float b[4] = {__uint_as_float(bu.x << 16), __uint_as_float(bu.x & 0xffff0000u),
                           __uint_as_float(bu.y << 16), __uint_as_float(bu.y & 0xffff0000u)};
-      v[j][0] = acc[0][j][0] * (asc * wsc.x) + b[0];
-      v[j][1] = acc[0][j][1] * (asc * wsc.y) + b[1];
-      v[j][2] = acc[0][j][2] * (asc * wsc.z) + b[2];
-      v[j][3] = acc[0][j][3] * (asc * wsc.w) + b[3];
+      v[j][0] = acc[j][0] * (asc * wsc.x) + b[0];
+      v[j][1] = acc[j][1] * (asc * wsc.y) + b[1];
+      v[j][2] = acc[j][2] * (asc * wsc.z) + b[2];
+      v[j][3] = acc[j][3] * (asc * wsc.w) + b[3];
       const float m = fmaxf(fmaxf(fabsf(v[j][0]), fabsf(v[j][1])), fmaxf(fabsf(v[j][2]), fabsf(v[j][3])));
       if (j / jph == 0) am0 = fmaxf(am0, m);
       else am1 = fmaxf(am1, m);
@@ -324,83 +324,62 @@ struct SkTile {
     }
   }
 
-  // Epilogue of fragment rows i0 .. i0 + ROWS - 1 of wave wid (each fragment: 4 consecutive
-  // columns of one row).  Every load the epilogue needs (bias, gate, the old z) is issued before
-  // the first store: the compiler cannot prove that the outputs do not alias the inputs, so an
-  // interleaved order would serialise one memory round trip per fragment.  Loads use indices
-  // clamped into the tile; values for rows or columns outside it are never stored.
-  template <int EPI, int ROWS, bool F8 = false>
-  HILO_DEV static void epilogue_rows(const GemmProblem &p, const TileRows &tr, int n0, int wid, int i0,
-                                     int lane, const f32x4 (&acc)[ROWS][TN]) {
-    const int rbase = (wid / WN) * (BM / WM) + i0 * 16 + (lane & 15);
+  // Epilogue of fragment row i0 of wave wid (each fragment: 4 consecutive columns of one row).  Loads use
+  // indices clamped into the tile; values for rows or columns outside it are never stored.
+  template <int EPI, bool F8>
+  HILO_DEV static void epilogue_row(const GemmProblem &p, const TileRows &tr, int n0, int wid, int i0, int lane,
+                                    const f32x4 (&acc)[TN]) {
+    const int rl = (wid / WN) * (BM / WM) + i0 * 16 + (lane & 15);
     const int cbase = n0 + (wid % WN) * (BN / WN) + CL * (lane >> 4);
+    const size_t m = size_t(tr.row0 + min(rl, tr.nrows - 1));
     const uint16_t *bias = reinterpret_cast<const uint16_t *>(p.bias[tr.sigma]);
     float bv[TN][4];
-    float4 gt[TN];
-    float4 zv[ROWS][TN];
+    float4 gt[TN], zv[TN], wsc[TN];
+    float asc;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int nc = min(cbase + j * CS, p.N - 4);
       const uint2 bu = *reinterpret_cast<const uint2 *>(bias + nc);
       bv[j][0] = __uint_as_float(bu.x << 16); bv[j][1] = __uint_as_float(bu.x & 0xffff0000u);
       bv[j][2] = __uint_as_float(bu.y << 16); bv[j][3] = __uint_as_float(bu.y & 0xffff0000u);
-      if constexpr (EPI == EPI_RESID)
+      if constexpr (EPI == EPI_RESID) {
         gt[j] = *reinterpret_cast<const float4 *>(p.mod + (size_t(tr.s * 2 + tr.sigma) * 6 + p.gate_idx) * p.D + nc);
-    }
-    float4 wsc[TN];
-    float asc[ROWS];
-    if constexpr (F8) {
-      const float *ws = tr.sigma ? p.w_scale[1] : p.w_scale[0];
-#pragma unroll
-      for (int j = 0; j < TN; ++j) wsc[j] = *reinterpret_cast<const float4 *>(ws + min(cbase + j * CS, p.N - 4));
-#pragma unroll
-      for (int i = 0; i < ROWS; ++i) asc[i] = p.a_scale[tr.row0 + min(rbase + i * 16, tr.nrows - 1)];
-    }
-    if constexpr (EPI == EPI_RESID) {
-#pragma unroll
-      for (int i = 0; i < ROWS; ++i) {
-        const size_t m = size_t(tr.row0 + min(rbase + i * 16, tr.nrows - 1));
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          zv[i][j] = *reinterpret_cast<const float4 *>(p.z + m * p.ldz + min(cbase + j * CS, p.N - 4));
+        zv[j] = *reinterpret_cast<const float4 *>(p.z + m * p.ldz + nc);
       }
+      if constexpr (F8) wsc[j] = *reinterpret_cast<const float4 *>((tr.sigma ? p.w_scale[1] : p.w_scale[0]) + nc);
     }
+    if constexpr (F8) asc = p.a_scale[m];
+    if (rl >= tr.nrows) return;
 #pragma unroll
-    for (int i = 0; i < ROWS; ++i) {
-      const int rl = rbase + i * 16;
-      if (rl >= tr.nrows) continue;
-      const size_t m = size_t(tr.row0 + rl);
+    for (int j = 0; j < TN; ++j) {
+      const int n = cbase + j * CS;
+      if (n >= p.N) continue;
+      float v[4];
+      if constexpr (F8) {
+        v[0] = acc[j][0] * (asc * wsc[j].x) + bv[j][0];
+        v[1] = acc[j][1] * (asc * wsc[j].y) + bv[j][1];
+        v[2] = acc[j][2] * (asc * wsc[j].z) + bv[j][2];
+        v[3] = acc[j][3] * (asc * wsc[j].w) + bv[j][3];
+      } else {
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int n = cbase + j * CS;
-        if (n >= p.N) continue;
-        float v[4];
-        if constexpr (F8) {
-          v[0] = acc[i][j][0] * (asc[i] * wsc[j].x) + bv[j][0];
-          v[1] = acc[i][j][1] * (asc[i] * wsc[j].y) + bv[j][1];
-          v[2] = acc[i][j][2] * (asc[i] * wsc[j].z) + bv[j][2];
-          v[3] = acc[i][j][3] * (asc[i] * wsc[j].w) + bv[j][3];
-        } else {
+        for (int e = 0; e < 4; ++e) v[e] = acc[j][e] + bv[j][e];
+      }
+      if constexpr (EPI == EPI_RESID) {
+        float4 zn = zv[j];
+        zn.x += gt[j].x * v[0];
+        zn.y += gt[j].y * v[1];
+        zn.z += gt[j].z * v[2];
+        zn.w += gt[j].w * v[3];
+        *reinterpret_cast<float4 *>(p.z + m * p.ldz + n) = zn;
+      } else {
+        if constexpr (EPI == EPI_GELU) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = acc[i][j][e] + bv[j][e];
+          for (int e = 0; e < 4; ++e) v[e] = gelu_tanh(v[e]);
         }
-        if constexpr (EPI == EPI_RESID) {
-          float4 zn = zv[i][j];
-          zn.x += gt[j].x * v[0];
-          zn.y += gt[j].y * v[1];
-          zn.z += gt[j].z * v[2];
-          zn.w += gt[j].w * v[3];
-          *reinterpret_cast<float4 *>(p.z + m * p.ldz + n) = zn;
-        } else {
-          if constexpr (EPI == EPI_GELU) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = gelu_tanh(v[e]);
-          }
-          uint2 u;
-          u.x = pack_bf16x2(v[0], v[1]);
-          u.y = pack_bf16x2(v[2], v[3]);
-          *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(p.out) + m * p.ldo + n) = u;
-        }
+        uint2 u;
+        u.x = pack_bf16x2(v[0], v[1]);
+        u.y = pack_bf16x2(v[2], v[3]);
+        *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(p.out) + m * p.ldo + n) = u;
       }
     }
   }
@@ -449,8 +428,8 @@ HILO_DEV void g2lds4(const void *g, void *lds_wave_base) {
 // the loads, reads and MFMA time per window are those of bf16.  256 x 256 tiles: v_mfma_f32_32x32x64_f8f6f4
 // per half (16 x 16 x 128 fragments of 32 bytes a lane would not fit twice), on 4 x 2 waves so that a wave
 // holds whole heads.  192 x 192 tiles: v_mfma_f32_16x16x128_f8f6f4 per window (the wave's 96 x 48 is not
-// whole 32 x 32 blocks).  64 x 64 step with the FP8 block 606 -> 586 us against one wave per SIMD, MLP half
-// on 7680 rows 697 -> 690.
+// whole 32 x 32 blocks).  Against one wave per SIMD the 64 x 64 step with the FP8 block went 597 -> 577 us; the
+// MLP half on 7680 rows is level (689 and 684, noise 0.3% and more between boxes).
 namespace g8 {
 // A BM x BN tile of bf16 or FP8 operands on 8 waves: WM x WN waves, MB x NB blocks of 16 x 16 each (B32: of
 // 32 x 32).
@@ -1164,9 +1143,9 @@ HILO_DEV void gemm_fix(const GemmProblem &p, const SkPlan &q) {
   for (int x = blockIdx.x * FW + (threadIdx.x >> 6); x < items; x += gridDim.x * FW) {
     const int f = x / (NW * TM), rem = x - f * (NW * TM), wid = rem / TM, i = rem - wid * TM;
     const int t = q.s > 1 ? f : q.dp + f;
-    f32x4 acc[1][TN];
+    f32x4 acc[TN];
 #pragma unroll
-    for (int j = 0; j < TN; ++j) acc[0][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < TN; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float *b[kFixBatch];
     int nb = 0;
     auto flush = [&]() {
@@ -1181,7 +1160,7 @@ HILO_DEV void gemm_fix(const GemmProblem &p, const SkPlan &q) {
       for (int c = 0; c < kFixBatch; ++c)
         if (c < nb) {
 #pragma unroll
-          for (int j = 0; j < TN; ++j) acc[0][j] += v[c][j];
+          for (int j = 0; j < TN; ++j) acc[j] += v[c][j];
         }
       nb = 0;
     };
@@ -1229,11 +1208,11 @@ HILO_DEV void gemm_fix(const GemmProblem &p, const SkPlan &q) {
     const TileRows tr = decode_row_tile(p, BM, rt);
     if constexpr (F8 && EPI == EPI_BIAS && BN == 256) {
       if (p.qk8 != nullptr && tn * BN < 2 * p.D) {
-        T::epilogue_rows_qk8(p, tr, tn * BN, wid, i, lane, acc);
+        T::epilogue_row_qk8(p, tr, tn * BN, wid, i, lane, acc);
         continue;
       }
     }
-    T::template epilogue_rows<EPI, 1, F8>(p, tr, tn * BN, wid, i, lane, acc);
+    T::template epilogue_row<EPI, F8>(p, tr, tn * BN, wid, i, lane, acc);
   }
 }
 
