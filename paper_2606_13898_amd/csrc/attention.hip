@@ -3,7 +3,7 @@
 //
 // bf16 path (gfx950 MFMA v_mfma_f32_16x16x32_bf16, fp32 online softmax in base 2):
 //   workgroup = NW waves x QW query rows of one (sample, head) (head dim 128: 8 x 32, one
-//   workgroup per CU; 64: 4 x 32, three per CU); K/V stream through LDS in tiles of 64 keys, double
+//   workgroup per CU; 64: 4 x 32, up to three per CU); K/V stream through LDS in tiles of 64 keys, double
 //   buffered.  Each wave computes S^T = K Q^T so that every lane owns one query
 //   row's scores (4 keys per 16-key subtile): the running max stays lane-local, and the
 //   probabilities are already in the register layout of the second MFMA operand for
@@ -25,8 +25,9 @@ namespace hilo {
 constexpr float kLog2e = 1.4426950408889634f;
 // online softmax: the reference maximum lags the true one by at most this much (base 2)
 constexpr float kLazyRescale = 8.0f;
-// short problems: the reference falls to a tile's own maximum while the row sum in its units stays below this
-constexpr float kTightSum = 65536.0f;
+// short problems: the reference falls to a tile's own maximum as far as the row sum in its units stays below
+// two to this
+constexpr float kTightRoom = 16.0f;
 
 // max with the lanes 16 and 32 apart (the 4 lanes holding the same query row)
 HILO_DEV float xmax16_32(float x) {
@@ -155,19 +156,27 @@ HILO_DEV AttnUnit attn_unit(const int *cu, int B, int heads, int BQ, long long i
   return AttnUnit{0, 0, 0, 1, 0};
 }
 
+// Two workgroups per CU at head dim 64 (whose grid holds three), the one of the grid at 128.
+template <int HD>
+HILO_DEV uint32_t attn_base(uint32_t grid) { return HD == 128 ? grid : grid - grid / 3; }
+
 // Workgroups that share I key steps (both the core and the merge derive it).  A range costs its steps, a cut
 // unit one partial per range to write and merge in turn, so a small problem goes to ranges of a few steps
 // rather than to every CU: at least 2, and up to 8 (head dim 64) or 4 (128) from 512 or 256 steps on.
-// Measured against one range per workgroup of the grid (core and merge): head dim 64, 24 heads x 600 tokens
-// 25.6 -> 20.3 us (4 steps 21.4, 16 steps 26.5), 4 x 1100 29.0 -> 18.7, 2 x (320 + 361) 17.0 -> 12.4 (4 steps
-// 14.7); head dim 128, 24 x 600 37.4 -> 32.7 (8 steps 36.9), 8 x 704 38.5 -> 32.0, 2 x (320 + 361) 25.9 -> 23.2.
+// Measured against one range for each of two (head dim 64) or one workgroups per CU: head dim 64, 24 heads x 600
+// tokens 25.1 -> 21.1 us, 2 x (320 + 361) 17.1 -> 11.9; head dim 128, 24 x 600 37.0 -> 31.3, 8 x 704 38.3 -> 26.4,
+// 2 x (320 + 361) 25.9 -> 17.5.  Head dim 64 goes to the third workgroup per CU only from 40 steps a range on: the
+// partials of 768 ranges cost more than they hide below (10800 steps 45.2 us against 43.7 on 512 ranges, 17328
+// steps 60.5 / 59.1, 23232 steps 74.2 / 74.5, 36960 steps 104.5 / 108).
 template <int HD>
 HILO_DEV int attn_parts(long long I, uint32_t grid) {
   constexpr uint32_t most = HD == 128 ? 4 : 8;
-  if (I >= (long long)most * grid) return grid;
+  const uint32_t base = attn_base<HD>(grid);
+  if (HD == 64 && I >= 40ll * base) return grid;
+  if (I >= (long long)most * base) return base;
   const uint32_t i = uint32_t(I), s = min(max(i / 64, 2u), most);
   // uniform, as the loops over its ranges must stay (the division runs on the vector ALU)
-  return __builtin_amdgcn_readfirstlane(min((i + s - 1) / s, grid));
+  return __builtin_amdgcn_readfirstlane(min((i + s - 1) / s, base));
 }
 
 struct AttnArgs {
@@ -223,7 +232,7 @@ HILO_DEV void attn_store_out(const AttnArgs &a, const AttnUnit &u, int wid, int 
 }
 
 // Head dim 64 has registers for three workgroups of 4 waves per CU (at most 168 each), which hide more of
-// each other's softmax than two: 24 heads x 7680 tokens 471 -> 436 us, 2766 tokens level.
+// each other's softmax than two: 24 heads x 7680 tokens 448 -> 411 us, 2766 tokens level.
 template <int HD, int QW, int NW, bool F8S>
 __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 3) void k_attn_bf16(AttnArgs a) {
   using S = AttnShape<HD, QW, NW>;
@@ -251,10 +260,10 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 3) void k_attn_bf16(AttnArgs
   // A short problem's output is rounded least where each tile's largest probability is 1, which bf16 holds
   // exactly, as it is when every range is a single tile.  Ranges of several tiles keep that by moving the
   // reference to every tile's own maximum, up or down: relative error of the output 0.00207-0.00210 instead of
-  // 0.0022-0.0023 with the lagging reference (bf16 rounding of the output alone 0.00166), at 0-0.7 us of a
-  // 12-31 us call.  A range per workgroup or longer keeps the lagging reference: 0.00233 either way.
-  const bool tight = P < int(gridDim.x);
-  const float lag = tight ? -INFINITY : kLazyRescale, fall = tight ? kTightSum : -1.0f;
+  // 0.0022-0.0023 with the lagging reference (bf16 rounding of the output alone 0.00166), at 0-1.2 us of a
+  // 12-36 us call.  Longer problems keep the lagging reference: 0.00233 either way.
+  const bool tight = P < int(attn_base<HD>(gridDim.x));
+  const float lag = tight ? -INFINITY : kLazyRescale, room = tight ? kTightRoom : 0.0f;
   const int pid = xcd_remap(blockIdx.x, P);
   const long long beg = I * pid / P, end = I * (pid + 1) / P;
   if (beg >= end) return;
@@ -508,8 +517,8 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 1 : 3) void k_attn_bf16(AttnArgs
         // kLazyRescale: O and l share it, so the result does not depend on it but for the rounding of P,
         // and the probabilities stay below 2^kLazyRescale.  Short problems (lag -inf): to this tile's maximum
         if (__any(mt > mrun[qs] + lag)) {
-          float mnew = fmaxf(mrun[qs], mt);
-          if (lacc[qs][0] * __builtin_amdgcn_exp2f(mrun[qs] - mt) < fall) mnew = mt;
+          const float fall = fmaxf(room - float(__builtin_amdgcn_frexp_expf(lacc[qs][0])), 0.f);
+          const float mnew = fmaxf(mrun[qs] - fall, mt);
           const float alpha = __builtin_amdgcn_exp2f(mrun[qs] - mnew);
           lacc[qs] *= alpha;
 #pragma unroll

@@ -32,10 +32,12 @@ def test_attention_core_f32(hd, lens, heads):
 
 # the bf16 core gives a problem of I key steps (units of 128 or 256 queries x tiles of 64 keys) to ranges of 2
 # to 4 or 8 steps: an empty one, a single step, odd counts around 2 steps a range, the growing range (128 to 512
-# steps), and the last size below one range per workgroup of the grid
+# steps), and the last size below a range for every workgroup; head dim 64 then has 512 ranges (5808 steps) and
+# 768 (22704)
 @pytest.mark.parametrize("hd,lens,heads", [(64, [0], 2), (64, [1], 2), (64, [65, 0, 129], 1), (64, [320, 361], 2),
-                                           (64, [1100], 4), (64, [600], 24), (128, [1], 2), (128, [193, 64], 3),
-                                           (128, [257, 320], 2), (128, [704], 8), (128, [600], 24)])
+                                           (64, [1100], 4), (64, [600], 24), (64, [1400], 24), (64, [2700], 24),
+                                           (128, [1], 2), (128, [193, 64], 3), (128, [257, 320], 2),
+                                           (128, [704], 8), (128, [600], 24)])
 def test_attention_core_bf16(hd, lens, heads):
     print(f"[kernel] bf16 attention core hd={hd} heads={heads} lens={lens}", flush=True)
     cu, D = _cu(lens), heads * hd
