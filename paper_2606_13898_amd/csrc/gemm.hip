@@ -970,8 +970,8 @@ HILO_DEV void gemm8_run(const GemmProblem &p, const SkPlan &q, int pid, uint8_t 
 // Small problems: 64 x 32 tiles, four waves each (a workgroup holds two), K split over the four in steps of
 // 64 and their sums added through LDS.  Fragments come straight from global memory: lane (lr, lg) takes
 // the 32 bytes at 32 lg of a row's 128-byte K step, two chunks for two MFMAs (any order of K will do as
-// long as both operands agree).  What bounds it is the latency of one tile, about 3 us plus 1.2 us per
-// 256 of K, or 2.7 where both tiles are busy (12 KB of fragments per step and wave at the L2-to-CU rate), so it is the better plan where
+// long as both operands agree).  What bounds it is the latency of one tile, about 3 us plus 1.4 us per
+// 256 of K, or 2.65 where both tiles are busy (12 KB of fragments per step and wave at the L2-to-CU rate), so it is the better plan where
 // 192 x 192 tiles would leave most CUs idle for a long K: 2 x ~320 rows, D 256, MLP 1024: QKV 14.4 -> 9.1
 // us by event pairs, output 20.6 -> 8.1, MLP up 17.2 -> 9.7, MLP down 28.6 -> 12.1; at 704 rows, D 1024, it
 // still wins for the output (34.5 -> 18 us) and MLP down (73 -> 49), and loses for QKV (26 against 36).
@@ -1052,22 +1052,27 @@ HILO_DEV void gemm_small_run(const GemmProblem &p, int rows, int pid, uint8_t *l
 }
 
 // The tile of a projection, chosen on the device (only it knows the row counts; the main kernel and the
-// fixup derive the same one): the shorter of two estimates in units of 10 ns, from measured rounds.  A
-// K step takes 1.46 us on a 256 x 256 tile and 0.91 on 192 x 192; a tile adds its prologue and epilogue,
-// 7 and 4 us, or 40 and 16 where it updates z (every workgroup reads and writes its tile's z at once, 26
-// and 14 us at the copy rate).  A plan that cuts tiles spreads the K steps evenly and adds its partials and
-// their fixup, about 30 and 20 us; a turn of TILE_SMALL is described at gemm_small_run.  2766 rows of a 64 x
-// 64 grid: 192 x 192 for all four projections (QKV 151 us against 168, output 70 / 108, MLP up 196 / 198,
-// MLP down 188 / 223); 25000 rows in 8 samples: 256 x 256 (QKV 1208 against 1256, MLP up 1535 / 1660, MLP
-// down 1600 / 1658) but for the output, which 256 x 256 would do in 515 against 533.  The cost of a tile that
-// updates z measured 33 to 45 us over D 1024 .. 4096 and 700 .. 25000 rows; at 34, which would give that
-// output to 256 x 256, D 1536 at 6300 rows (74 us against 65) and MLP down of D 3072 at 3100 rows (281
-// against 245) would go there too.
+// fixup derive the same one): the shortest of three estimates in units of 10 ns, fitted to forced runs of each
+// tile over D 256 .. 4096 and 64 .. 25000 rows (616 projections; the choice loses 0.5% to the best tile on average,
+// 1.5% without the terms for a launch and for pieces without a tail).  A K step takes 1.46 us on a 256 x 256 tile
+// and 0.91 on 192 x 192; a tile adds its epilogue, 7 and 4 us, or 34 and 14 where it updates z (every workgroup
+// reads and writes its tile's z at once, 26 and 14 us at the copy rate); a launch of whole tiles 7 us (3 where they
+// update z).  A plan that cuts tiles spreads the K steps evenly and adds its partials and their fixup, about 36 and
+// 20 us, 12 less where the pieces of T tiles (T a power of two) fill the workgroups without a tail.  A turn of
+// TILE_SMALL takes 1.4 us per four K steps, or 2.65 with two tiles a workgroup, and 3.  2766 rows of a 64 x 64
+// grid: 192 x 192 for all four projections (QKV 151 us against 168, output 70 / 108, MLP up 196 / 198, MLP down 188
+// / 223); 25000 rows in 8 samples: 256 x 256 (QKV 1208 against 1256, output 515 / 533, MLP up 1535 / 1660, MLP down
+// 1600 / 1658); D 1536, MLP down at 200 rows: 192 x 192 in 16 pieces (32 us; small tiles 40).
+struct TileCost {
+  uint32_t step, tile, tile_z, cut;
+};
+
 template <int EPI>
-HILO_DEV uint32_t plan_cost(uint32_t T, uint32_t nk, uint32_t step, uint32_t tile, uint32_t tile_z, uint32_t cut) {
+HILO_DEV uint32_t plan_cost(uint32_t T, uint32_t nk, TileCost c) {
   constexpr uint32_t P = kGemmWorkgroups;
-  const uint32_t rounds = (T + P - 1) / P, t = EPI == EPI_RESID ? tile_z : tile;
-  return runs_whole(T, nk) ? rounds * (nk * step + t) : T * nk / P * step + rounds * t + cut;
+  const uint32_t rounds = (T + P - 1) / P, t = EPI == EPI_RESID ? c.tile_z : c.tile;
+  if (runs_whole(T, nk)) return rounds * (nk * c.step + t) + (EPI == EPI_RESID ? 300 : 700);
+  return T * nk / P * c.step + rounds * t + c.cut - (T < P && (T & (T - 1)) == 0 ? 1200 : 0);
 }
 
 enum Tile { TILE_192, TILE_256, TILE_SMALL };
@@ -1085,10 +1090,10 @@ HILO_DEV Tile choose_tile(const GemmProblem &p, int &rows) {
     r256 += (img + 255) / 256 + (p.L + 255) / 256;
   }
   const uint32_t nk = p.K / 64, tiles = uint32_t(r64) * (p.N / 32);
-  uint32_t best = plan_cost<EPI>(r192 * ((p.N + 191) / 192), nk, 91, 400, 1600, 2000);
+  uint32_t best = plan_cost<EPI>(r192 * ((p.N + 191) / 192), nk, TileCost{91, 400, 1400, 2000});
   rows = r192;
   Tile t = TILE_192;
-  const uint32_t c256 = plan_cost<EPI>(r256 * ((p.N + 255) / 256), nk, 146, 700, 4000, 3000);
+  const uint32_t c256 = plan_cost<EPI>(r256 * ((p.N + 255) / 256), nk, TileCost{146, 700, 3400, 3600});
   if (c256 < best) {
     best = c256;
     rows = r256;
@@ -1096,7 +1101,7 @@ HILO_DEV Tile choose_tile(const GemmProblem &p, int &rows) {
   }
   // a turn takes 2 tiles a workgroup; with one the K steps run twice as fast
   const uint32_t turns = (tiles + 2 * P - 1) / (2 * P);
-  if (turns * ((nk + 3) / 4 * (tiles <= P ? 120 : 270) + 300) < best) {
+  if (turns * ((nk + 3) / 4 * (tiles <= P ? 140 : 265) + 300) < best) {
     rows = r64;
     t = TILE_SMALL;
   }

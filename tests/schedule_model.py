@@ -9,8 +9,9 @@ WORKGROUPS = 256      # kGemmWorkgroups
 NO_SPLIT_STEPS = 64   # kNoSplitSteps
 MIN_STEPS = 12        # kSkMinSteps
 # estimates of choose_tile in units of 10 ns: a K step, a tile, a tile that updates z, cut tiles and their fixup
-TILE_COSTS = {192: (91, 400, 1600, 2000), 256: (146, 700, 4000, 3000)}
-SMALL_COSTS = (120, 270, 300)  # four K steps with one tile a workgroup, with two, a turn
+TILE_COSTS = {192: (91, 400, 1400, 2000), 256: (146, 700, 3400, 3600)}
+SMALL_COSTS = (140, 265, 300)  # four K steps with one tile a workgroup, with two, a turn
+LAUNCH_Z, LAUNCH, NO_TAIL = 300, 700, 1200  # a launch of whole tiles that update z or don't; pieces without a tail
 
 
 def whole_tiles(T, P, nk):
@@ -48,7 +49,9 @@ def cost(resid, T, nk, step, tile, tile_z, cut):
     """plan_cost, in units of 10 ns."""
     P = WORKGROUPS
     rounds, t = -(-T // P), tile_z if resid else tile
-    return rounds * (nk * step + t) if whole_tiles(T, P, nk) else T * nk // P * step + rounds * t + cut
+    if whole_tiles(T, P, nk):
+        return rounds * (nk * step + t) + (LAUNCH_Z if resid else LAUNCH)
+    return T * nk // P * step + rounds * t + cut - (NO_TAIL if T < P and T & (T - 1) == 0 else 0)
 
 
 def choose(segments, N, K, resid):
@@ -92,10 +95,10 @@ def fixup_skipped(max_img_rows, text, batch, N, K, tile=192, kstep=64):
 
 # (dim, mlp_dim, sample lengths, text rows), and the plans of MLP up and down
 MLP_SHAPES = [
-    # 64 x 32 tiles: K of one, three, five and fifteen steps over four waves, one turn; 26 tiles of one K step
+    # 64 x 32 tiles: K of one, three, five and fifteen steps over four waves, one turn; 192 x 192 of one K step
     ((64, 320, [193, 65], 31), dict(up=("small", 60, 1), down=("small", 12, 1))),
     ((192, 960, [705, 64, 1], 0), dict(up=("small", 420, 1), down=("small", 84, 1))),
-    ((64, 320, [1100, 901], 31), dict(up=(192, 26, 1, 26, 0, 256), down=("small", 66, 1))),
+    ((64, 1024, [1100, 901], 31), dict(up=(192, 78, 1, 78, 0, 256), down=("small", 66, 1))),
     # 64 x 32 tiles in two turns
     ((256, 1088, [2100], 40), dict(up=(192, 72, 1, 72, 0, 256), down=("small", 272, 1))),
     ((640, 1024, [1640], 40), dict(up=(192, 60, 1, 60, 0, 256), down=("small", 520, 2))),
@@ -126,23 +129,23 @@ BLOCK_SHAPES = {
                          down=(192, 34, 8, 256, 16, 16))),
     # QKV in 2 pieces, their tail of 40 over 124 workgroups; the output in 6
     "k_pieces": (BlockShape(1, 1, 12, 12, 40, 4736, 37, 128, 1024, "bf16"),
-                 dict(qkv=(192, 148, 2, 256, 40, 124), o=(192, 50, 6, 256, 44, 48), up=("small", 128, 1),
-                      down=("small", 592, 2))),
+                 dict(qkv=(192, 148, 2, 256, 40, 124), o=(192, 50, 6, 256, 44, 48),
+                      up=(192, 12, 22, 256, 8, 8), down=("small", 592, 2))),
     # QKV on 256 x 256 in 5 pieces, their tail cut
-    "k_pieces_256": (BlockShape(1, 1, 14, 14, 0, 4864, 38, 128, 1024, "bf16"),
-                     dict(qkv=(256, 57, 5, 256, 29, 39), o=(192, 52, 5, 256, 4, 6), up=("small", 128, 1),
-                          down=("small", 608, 2))),
+    "k_pieces_256": (BlockShape(1, 1, 14, 14, 0, 5120, 40, 128, 1024, "bf16"),
+                     dict(qkv=(256, 60, 5, 256, 44, 59), o=(192, 54, 5, 256, 14, 19), up=(192, 12, 22, 256, 8, 8),
+                          down=("small", 640, 2))),
 }
 
 # The MLP half with K pieces, every row compared
 SPLIT_K_SHAPES = {
     # MLP down in 10 pieces plus a stream-K tail of 14 units over 16 workgroups; MLP up in two waves
     "pieces_and_tail": (BlockShape(3, 1, 16, 20, 40, 512, 4, 128, 8192, "bf16"),
-                        dict(qkv=(192, 72, 1, 72, 0, 256), o=("small", 288, 1), up=(192, 387, 1, 387, 0, 256),
+                        dict(qkv=("small", 864, 2), o=("small", 288, 1), up=(192, 387, 1, 387, 0, 256),
                              down=(192, 27, 10, 256, 14, 16))),
     # a single 192 x 192 down-projection tile: every K piece is one step, the fixup sums 128 partial tiles
     "one_tile_128_pieces": (BlockShape(1, 1, 12, 12, 0, 192, 3, 64, 8192, "bf16"),
-                            dict(qkv=("small", 54, 1), o=("small", 18, 1), up=(192, 43, 1, 43, 0, 256),
+                            dict(qkv=("small", 54, 1), o=("small", 18, 1), up=("small", 768, 2),
                                  down=(192, 1, 128, 0, 128, 128))),
 }
 
