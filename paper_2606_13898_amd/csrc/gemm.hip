@@ -1053,18 +1053,21 @@ HILO_DEV void gemm_small_run(const GemmProblem &p, int rows, int pid, uint8_t *l
 
 // The tile of a projection, chosen on the device (only it knows the row counts; the main kernel and the
 // fixup derive the same one): the shortest of three estimates in units of 10 ns, fitted to forced runs of each
-// tile over D 256 .. 4096 and 64 .. 25000 rows (616 projections; the choice loses 0.5% to the best tile on average,
-// 1.5% without the terms for a launch and for pieces without a tail).  A K step takes 1.46 us on a 256 x 256 tile
-// and 0.91 on 192 x 192; a tile adds its epilogue, 7 and 4 us, or 34 and 14 where it updates z (every workgroup
-// reads and writes its tile's z at once, 26 and 14 us at the copy rate); a launch of whole tiles 7 us (3 where they
-// update z).  A plan that cuts tiles spreads the K steps evenly and adds its partials and their fixup, about 36 and
-// 20 us, 12 less where the pieces of T tiles (T a power of two) fill the workgroups without a tail.  A turn of
-// TILE_SMALL takes 1.4 us per four K steps, or 2.65 with two tiles a workgroup, and 3.  2766 rows of a 64 x 64
-// grid: 192 x 192 for all four projections (QKV 151 us against 168, output 70 / 108, MLP up 196 / 198, MLP down 188
-// / 223); 25000 rows in 8 samples: 256 x 256 (QKV 1208 against 1256, output 515 / 533, MLP up 1535 / 1660, MLP down
-// 1600 / 1658); D 1536, MLP down at 200 rows: 192 x 192 in 16 pieces (32 us; small tiles 40).
+// tile over D 256 .. 4096 and 64 .. 25000 rows (616 projections; the choice loses 0.4% to the best tile on average,
+// 1.5% without the terms for a launch and for the number of tiles cut into pieces).  A K step takes 1.46 us on a 256
+// x 256 tile and 0.91 on 192 x 192; a tile adds its epilogue, 7 and 4 us, or 33 and 14 where it updates z (every
+// workgroup reads and writes its tile's z at once, 26 and 14 us at the copy rate); a launch of whole tiles 7 us (3
+// where they update z); a stream-K tail 36 and 20 us for its partials and their fixup.  K pieces spread the K steps
+// evenly; their partials, the fixup and z take 45 us and 0.35 a tile, or 27 and 0.2, and 45 or 25 where the pieces of
+// T tiles (T a power of two) fill the workgroups without a tail.  A turn of TILE_SMALL takes 1.4 us per four K steps,
+// or 2.65 with two tiles a workgroup, and 3.  2766 rows of a 64 x 64 grid: 192 x 192 for all four projections (QKV
+// 151 us against 168, output 70 / 108, MLP up 196 / 198, MLP down 188 / 223); 25000 rows in 8 samples: 256 x 256 (QKV
+// 1208 against 1256, output 515 / 533, MLP up 1535 / 1660, MLP down 1600 / 1658); D 1536, MLP down at 200 rows: 192 x
+// 192 in 16 pieces (32 us; small tiles 40).
 struct TileCost {
-  uint32_t step, tile, tile_z, cut;
+  uint32_t step, tile, tile_z;     // a K step, a tile, a tile that updates z
+  uint32_t tail;                   // the partials of a tail
+  uint32_t piece, piece_t, even;   // those of K pieces: in all, per tile; in all without a tail
 };
 
 template <int EPI>
@@ -1072,7 +1075,9 @@ HILO_DEV uint32_t plan_cost(uint32_t T, uint32_t nk, TileCost c) {
   constexpr uint32_t P = kGemmWorkgroups;
   const uint32_t rounds = (T + P - 1) / P, t = EPI == EPI_RESID ? c.tile_z : c.tile;
   if (runs_whole(T, nk)) return rounds * (nk * c.step + t) + (EPI == EPI_RESID ? 300 : 700);
-  return T * nk / P * c.step + rounds * t + c.cut - (T < P && (T & (T - 1)) == 0 ? 1200 : 0);
+  const uint32_t steps = T * nk / P * c.step;
+  if (T >= P) return steps + rounds * t + c.tail;
+  return steps + ((T & (T - 1)) == 0 ? c.even : c.piece + c.piece_t * T);
 }
 
 enum Tile { TILE_192, TILE_256, TILE_SMALL };
@@ -1090,10 +1095,10 @@ HILO_DEV Tile choose_tile(const GemmProblem &p, int &rows) {
     r256 += (img + 255) / 256 + (p.L + 255) / 256;
   }
   const uint32_t nk = p.K / 64, tiles = uint32_t(r64) * (p.N / 32);
-  uint32_t best = plan_cost<EPI>(r192 * ((p.N + 191) / 192), nk, TileCost{91, 400, 1400, 2000});
+  uint32_t best = plan_cost<EPI>(r192 * ((p.N + 191) / 192), nk, TileCost{91, 400, 1400, 2000, 2700, 20, 2500});
   rows = r192;
   Tile t = TILE_192;
-  const uint32_t c256 = plan_cost<EPI>(r256 * ((p.N + 255) / 256), nk, TileCost{146, 700, 3400, 3600});
+  const uint32_t c256 = plan_cost<EPI>(r256 * ((p.N + 255) / 256), nk, TileCost{146, 700, 3300, 3600, 4500, 35, 4500});
   if (c256 < best) {
     best = c256;
     rows = r256;

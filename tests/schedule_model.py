@@ -8,10 +8,11 @@ from paper_2606_13898_amd.inputs import BlockShape
 WORKGROUPS = 256      # kGemmWorkgroups
 NO_SPLIT_STEPS = 64   # kNoSplitSteps
 MIN_STEPS = 12        # kSkMinSteps
-# estimates of choose_tile in units of 10 ns: a K step, a tile, a tile that updates z, cut tiles and their fixup
-TILE_COSTS = {192: (91, 400, 1400, 2000), 256: (146, 700, 3400, 3600)}
+# estimates of choose_tile in units of 10 ns: a K step, a tile, a tile that updates z, the partials of a tail, of K
+# pieces in all, per tile, and in all without a tail
+TILE_COSTS = {192: (91, 400, 1400, 2000, 2700, 20, 2500), 256: (146, 700, 3300, 3600, 4500, 35, 4500)}
 SMALL_COSTS = (140, 265, 300)  # four K steps with one tile a workgroup, with two, a turn
-LAUNCH_Z, LAUNCH, NO_TAIL = 300, 700, 1200  # a launch of whole tiles that update z or don't; pieces without a tail
+LAUNCH_Z, LAUNCH = 300, 700  # a launch of whole tiles that update z or don't
 
 
 def whole_tiles(T, P, nk):
@@ -45,13 +46,16 @@ def row_tiles(segments, tile):
     return sum(-(-n // tile) for seg in segments for n in seg)
 
 
-def cost(resid, T, nk, step, tile, tile_z, cut):
+def cost(resid, T, nk, step, tile, tile_z, tail, piece, piece_t, even):
     """plan_cost, in units of 10 ns."""
     P = WORKGROUPS
     rounds, t = -(-T // P), tile_z if resid else tile
     if whole_tiles(T, P, nk):
         return rounds * (nk * step + t) + (LAUNCH_Z if resid else LAUNCH)
-    return T * nk // P * step + rounds * t + cut - (NO_TAIL if T < P and T & (T - 1) == 0 else 0)
+    steps = T * nk // P * step
+    if T >= P:
+        return steps + rounds * t + tail
+    return steps + (even if T & (T - 1) == 0 else piece + piece_t * T)
 
 
 def choose(segments, N, K, resid):
@@ -110,8 +114,8 @@ MLP_SHAPES = [
     ((2048, 3648, [5000], 0), dict(up=(192, 513, 1, 512, 1, 3), down=(192, 297, 1, 256, 41, 195))),
     # 192 x 192 in five waves of whole tiles; 19 pieces, their tail cut
     ((64, 16384, [2500], 0), dict(up=(192, 1204, 1, 1204, 0, 256), down=(192, 14, 19, 256, 10, 12))),
-    # 256 x 256: a tail of 16 tiles over 43 workgroups; K pieces whose tail is cut (residual)
-    ((2048, 13312, [5100], 0), dict(up=(256, 1040, 1, 1024, 16, 43), down=(256, 160, 2, 256, 64, 256))),
+    # 256 x 256: a tail of 16 tiles over 32 workgroups; K pieces whose tail is cut (residual)
+    ((1536, 13312, [5000], 0), dict(up=(256, 1040, 1, 1024, 16, 32), down=(256, 120, 3, 256, 104, 256))),
     # 256 x 256 residual in one wave of whole tiles, and in two
     ((2560, 8192, [5540], 40), dict(up=(256, 736, 1, 736, 0, 256), down=(256, 230, 1, 230, 0, 256))),
     ((2048, 4096, [15000], 0), dict(up=(256, 944, 1, 944, 0, 256), down=(256, 472, 1, 472, 0, 256))),
@@ -130,10 +134,10 @@ BLOCK_SHAPES = {
     # QKV in 2 pieces, their tail of 40 over 124 workgroups; the output in 6
     "k_pieces": (BlockShape(1, 1, 12, 12, 40, 4736, 37, 128, 1024, "bf16"),
                  dict(qkv=(192, 148, 2, 256, 40, 124), o=(192, 50, 6, 256, 44, 48),
-                      up=(192, 12, 22, 256, 8, 8), down=("small", 592, 2))),
+                      up=("small", 128, 1), down=("small", 592, 2))),
     # QKV on 256 x 256 in 5 pieces, their tail cut
     "k_pieces_256": (BlockShape(1, 1, 14, 14, 0, 5120, 40, 128, 1024, "bf16"),
-                     dict(qkv=(256, 60, 5, 256, 44, 59), o=(192, 54, 5, 256, 14, 19), up=(192, 12, 22, 256, 8, 8),
+                     dict(qkv=(256, 60, 5, 256, 44, 59), o=(192, 54, 5, 256, 14, 19), up=("small", 128, 1),
                           down=("small", 640, 2))),
 }
 

@@ -29,7 +29,7 @@ def test_model_holds_the_kernels_constants():
     assert f"kNoSplitSteps = {M.NO_SPLIT_STEPS};" in src and f"kSkMinSteps = {M.MIN_STEPS};" in src
     for tile, costs in M.TILE_COSTS.items():
         assert re.search(rf"plan_cost<EPI>\(r{tile} \* .*, nk, TileCost\{{{', '.join(map(str, costs))}\}}\);", src), tile
-    assert f"(EPI == EPI_RESID ? {M.LAUNCH_Z} : {M.LAUNCH});" in src and f"(T & (T - 1)) == 0 ? {M.NO_TAIL} : 0);" in src
+    assert f"(EPI == EPI_RESID ? {M.LAUNCH_Z} : {M.LAUNCH});" in src
     assert "turns * ((nk + 3) / 4 * (tiles <= P ? {} : {}) + {}) < best".format(*M.SMALL_COSTS) in src
 
 
