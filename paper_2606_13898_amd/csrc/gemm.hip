@@ -879,7 +879,7 @@ HILO_DEV void gemm8_run(const GemmProblem &p, const SkPlan &q, int pid, uint8_t 
       // vmcnt, so a load issued behind them waits for them too.  Two batches of a 256 x 256 tile are 64
       // registers beside its 128 accumulators, a third would not fit (64 registers went to scratch, whose
       // accesses wait for each other and for the loads in flight); on 192 x 192 three are the whole tile.
-      // 25004 rows in 8 samples: output 541 -> 515 us, MLP down 1653 -> 1600 against the three that spilled.
+      // 25004 rows in 8 samples: output 559 -> 515 us, MLP down 1661 -> 1600 against the three that spilled.
       constexpr int ZR = EPI == EPI_RESID ? 2 : 1, ZS = NB == 4 ? 2 : 3;
       static_assert(MB % ZR == 0, "row blocks per batch");
       f32x4 z[ZS][ZR][NB];
